@@ -505,10 +505,18 @@ fk_status plan_launch(int precision, int64_t n_tasks, fk::LaunchCfg* cfg, bool b
         if (oe != hipSuccess || bpc <= 0)
             return fail(FK_EDEVICE, "occupancy query failed for block %d", l.block);
     }
+    // As many blocks as are resident, each wavefront with at least one walk.
+    // A launch with fewer walks than resident lanes gives every wavefront the
+    // same share of them (cap): the walks then run in shared drain rounds,
+    // where a wavefront takes 64 steps of work at a time however few walks it
+    // holds, and the longest walks have the most lanes to themselves.
     int64_t grid = (int64_t)cus * bpc;
-    const int64_t need = (n_tasks + l.block - 1) / l.block;
+    const int64_t waves = l.block / 64;
+    const int64_t need = (n_tasks + waves - 1) / waves;
     if (grid > need) grid = need;
     if (grid < 1) grid = 1;
+    const int64_t share = (n_tasks + grid * waves - 1) / (grid * waves);
+    cfg->cap = share < 64 ? (uint32_t)std::max<int64_t>(share, 1) : 64u;
     cfg->block = l.block;
     cfg->grid = (int)grid;
     cfg->grab = l.grab;
@@ -589,6 +597,7 @@ fk_status run_solve(int32_t kind, const double* stations, int64_t n_stations, co
         C.total_waves = (uint32_t)((int64_t)cfg.grid * cfg.block / 64);
         C.stripes = cfg.stripes;
         C.refill_cost = cfg.refill_cost;
+        C.cap = cfg.cap;
         std::pair<hipEvent_t, hipEvent_t> ev{nullptr, nullptr};
         const bool timed = timing && timing_begin(&ev, stream);
         if (p->precision == FK_F64) {
@@ -822,6 +831,7 @@ fk_status solve_batch(const fk_problem* probs, int32_t n, fk_stat* out, void* wo
         A.total_waves = (uint32_t)((int64_t)cfg.grid * cfg.block / 64);
         A.stripes = cfg.stripes;
         A.refill_cost = cfg.refill_cost;
+        A.cap = cfg.cap;
         std::pair<hipEvent_t, hipEvent_t> ev{nullptr, nullptr};
         const bool timed = timing_begin(&ev, stream);
         le = fk::launch_batch_walk(A, cfg, stream, loop, shared);
@@ -919,6 +929,7 @@ fk_status adjoint(int32_t kind, const double* stations, int64_t n_stations, cons
         cfg.grab = l.grab;
         cfg.stripes = 1;
         cfg.refill_cost = l.refill_cost > 0 ? (uint32_t)l.refill_cost : 64u;
+        cfg.cap = 64;
     } else if ((st = plan_launch(p->precision, L.n_tasks, &cfg, false, loop_kind(p, nullptr), false, true)) != FK_OK) {
         return st;
     }
@@ -931,6 +942,7 @@ fk_status adjoint(int32_t kind, const double* stations, int64_t n_stations, cons
     C.total_waves = (uint32_t)((int64_t)cfg.grid * cfg.block / 64);
     C.stripes = cfg.stripes;
     C.refill_cost = cfg.refill_cost;
+    C.cap = cfg.cap;
     C.counts = counts;
     C.fwd_steps = reinterpret_cast<const uint32_t*>(static_cast<const char*>(fwd_workspace) + L.steps);
     C.nvox = AL.nvox;

@@ -92,6 +92,7 @@ struct WalkCommon {
     uint32_t total_waves;      // resident wavefronts of the launch
     uint32_t stripes;          // claim counters of the queue (1 .. 32)
     uint32_t refill_cost;      // 128 x the start-up cost of the refill rule, in macro-steps
+    uint32_t cap;              // most live walks of a wavefront (1 .. 64)
     int32_t domain;            // FK_DOMAIN_BOX / FK_DOMAIN_BALL
     double ctr[3];             // ball domain: centre, squared radius, radius
     double r2;
@@ -189,6 +190,7 @@ struct BatchArgs {
     int32_t precision;
     uint32_t stripes;
     uint32_t refill_cost;
+    uint32_t cap;
     // uniform_key: every problem's generator key is (key0, key1)
     uint32_t key0, key1;
     int32_t uniform_key;
@@ -206,6 +208,7 @@ struct LaunchCfg {
     int grab;
     uint32_t stripes;
     uint32_t refill_cost;
+    uint32_t cap;
 };
 
 // Host launchers (one translation unit per kernel family).

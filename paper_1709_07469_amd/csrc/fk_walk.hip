@@ -24,11 +24,14 @@
 //   - drain rounds: once the queue is empty, all 64 lanes of a wavefront
 //     generate Philox blocks and normals for its remaining live walks into
 //     LDS (any lane can compute any walk's block, the generator being
-//     counter based), and the live lanes step through that buffer -- up to
-//     128 (FP64) or 256 (mixed) steps per round for a lone walk.  The longest
-//     walks, which decide when the launch ends, then cost a move and a test
-//     per step instead of a full random-number generation each, and partly
-//     idle wavefronts keep all lanes busy generating;
+//     counter based) -- up to 128 (FP64) or 256 (mixed) steps per round for a
+//     lone walk.  With few live walks the whole round is shared by the lanes
+//     (coop_round below): only the chains of positions run step after step,
+//     one lane per walk and axis, while densities and exit tests are taken
+//     for all steps at once.  The longest walks decide when a launch ends;
+//   - a launch of fewer walks than lanes gives every resident wavefront the
+//     same few walks (Queue::cap) instead of filling wavefronts one by one,
+//     and works in drain rounds from its start;
 //   - a walk's record is written to its own slot (task index), so the result
 //     does not depend on which lane or wavefront ran it, nor on the mode.
 #include <hip/hip_runtime.h>
@@ -68,6 +71,22 @@ __device__ __forceinline__ uint64_t first_lane_u64(uint64_t v)
     return ((uint64_t)hi << 32) | lo;
 }
 
+// The value lane l (the same for the whole wavefront) holds.
+__device__ __forceinline__ uint64_t lane_u64(uint64_t v, int l)
+{
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, l);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), l);
+    return ((uint64_t)hi << 32) | lo;
+}
+__device__ __forceinline__ double lane_value(double v, int l)
+{
+    return __longlong_as_double((long long)lane_u64((uint64_t)__double_as_longlong(v), l));
+}
+__device__ __forceinline__ float lane_value(float v, int l)
+{
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
+}
+
 __device__ __forceinline__ void wave_sync_lds()
 {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -83,6 +102,7 @@ struct Queue {
     uint32_t total_waves;
     uint32_t stripes;              // 1 .. kMaxStripes
     uint32_t refill_cost;          // 128 R of the refill rule below
+    uint32_t cap;                  // most live walks of a wavefront (1 .. 64)
 };
 
 struct Pool {
@@ -116,10 +136,12 @@ __device__ __forceinline__ uint64_t refill(Pool& pool, const Queue& Q, bool acti
 {
     pool.rounds += 1;
     const uint64_t idle = __ballot(!active);
-    if (idle == 0) return ~0ull;
-    const uint32_t n_idle = (uint32_t)__popcll(idle);
-    // an all-idle wavefront always passes: started <= 64 rounds
-    if (!pool.exhausted && pool.started > 0 &&
+    const uint32_t live = 64u - (uint32_t)__popcll(idle);
+    if (live >= Q.cap) return ~0ull;
+    const uint32_t n_idle = Q.cap - live;
+    // an all-idle wavefront always passes: started <= 64 rounds.  A capped
+    // launch is short and its rounds are many steps long: no waiting there.
+    if (Q.cap == 64u && !pool.exhausted && pool.started > 0 &&
         (uint64_t)n_idle * (n_idle + 1) * pool.rounds < (uint64_t)Q.refill_cost * (uint64_t)pool.started)
         return ~0ull;
     const uint32_t stripes = Q.stripes;
@@ -146,8 +168,8 @@ __device__ __forceinline__ uint64_t refill(Pool& pool, const Queue& Q, bool acti
     const uint64_t avail = pool.end - pool.next;
     const uint32_t rank = (uint32_t)__popcll(idle & __lanemask_lt());
     uint64_t mine = ~0ull;
-    if (!active && rank < avail) mine = pool.next + rank;
     const uint64_t taken = (n_idle < avail) ? n_idle : avail;
+    if (!active && rank < taken) mine = pool.next + rank;
     pool.next += taken;
     pool.started += (int64_t)taken;
     return mine;
@@ -350,7 +372,7 @@ struct Prec<true> {
     __device__ static GridProbe grid_fetch(const Src& s, T x, T y, T z) { return grid_fetch_f64<LEVELS>(s, x, y, z); }
     template <bool LEVELS>
     __device__ static T grid_keep(const Src& s, const GridProbe& p) { return grid_keep_f64<LEVELS>(s, p); }
-    __device__ static T bodies(const Src& s, T g, T x, T y, T z, int j0 = 0) { return bodies_f64(s, g, x, y, z, j0); }
+    __device__ static T bodies(const Src& s, T g, T x, T y, T z) { return bodies_f64(s, g, x, y, z); }
     __device__ static int64_t voxel(const Src& s, T x, T y, T z) { return voxel_f64(s, x, y, z); }
     __device__ static T lo(const WalkCommon& C, int c) { return C.lo[c]; }
     __device__ static T hi(const WalkCommon& C, int c) { return C.hi[c]; }
@@ -388,7 +410,7 @@ struct Prec<false> {
     __device__ static GridProbe grid_fetch(const Src& s, T x, T y, T z) { return grid_fetch_f32<LEVELS>(s, x, y, z); }
     template <bool LEVELS>
     __device__ static T grid_keep(const Src& s, const GridProbe& p) { return grid_keep_f32<LEVELS>(s, p); }
-    __device__ static T bodies(const Src& s, T g, T x, T y, T z, int j0 = 0) { return bodies_f32(s, g, x, y, z, j0); }
+    __device__ static T bodies(const Src& s, T g, T x, T y, T z) { return bodies_f32(s, g, x, y, z); }
     __device__ static int64_t voxel(const Src& s, T x, T y, T z) { return voxel_f32(s, x, y, z); }
     __device__ static T lo(const WalkCommon& C, int c) { return C.lo_f[c]; }
     __device__ static T hi(const WalkCommon& C, int c) { return C.hi_f[c]; }
@@ -494,6 +516,30 @@ struct LaneProblem {
         pid = c.problem_id;
         max_steps = c.max_steps;
     }
+
+    // Takes lane l's problem (the same in every lane afterwards).
+    __device__ __forceinline__ void from_lane(const LaneProblem& o, int l, bool keys)
+    {
+        C = (const WalkCommon*)lane_u64((uint64_t)o.C, l);
+        src = (const typename Prec<F64>::Src*)lane_u64((uint64_t)o.src, l);
+        sdt = lane_value(o.sdt, l);
+        lo0 = lane_value(o.lo0, l);
+        lo1 = lane_value(o.lo1, l);
+        lo2 = lane_value(o.lo2, l);
+        hi0 = lane_value(o.hi0, l);
+        hi1 = lane_value(o.hi1, l);
+        hi2 = lane_value(o.hi2, l);
+        dt = lane_value(o.dt, l);
+        delta = lane_value(o.delta, l);
+        ball = __builtin_amdgcn_readlane((int)o.ball, l) != 0;
+        bridge = __builtin_amdgcn_readlane((int)o.bridge, l) != 0;
+        if (keys) {
+            key0 = (uint32_t)__builtin_amdgcn_readlane((int)o.key0, l);
+            key1 = (uint32_t)__builtin_amdgcn_readlane((int)o.key1, l);
+        }
+        pid = (uint32_t)__builtin_amdgcn_readlane((int)o.pid, l);
+        max_steps = (int64_t)lane_u64((uint64_t)o.max_steps, l);
+    }
 };
 
 // The stepping loop a kernel instance is built for.  Bits 0-1: 0 = the box
@@ -531,10 +577,10 @@ struct Walker {
                y2 - P.lo2 >= P.delta && P.hi2 - y2 >= P.delta;
     }
 
-    // Brownian-bridge test of step m from (x0, x1, x2) to y (both inside):
-    // returns the face the walk stopped at (0..5; 6 = the sphere) or -1.
-    __device__ __forceinline__ int bridge_stop(const LaneProblem<F64>& P, uint32_t m, T x0, T x1, T x2, T y0, T y1,
-                                               T y2) const
+    // Brownian-bridge test of step m of the walk with counter words pctr and
+    // sctr, from (x0, x1, x2) to y (both inside): returns the face the walk stopped at (0..5; 6 = the sphere) or -1.
+    __device__ __forceinline__ static int bridge_stop(const LaneProblem<F64>& P, uint32_t pctr, uint32_t sctr,
+                                                      uint32_t m, T x0, T x1, T x2, T y0, T y1, T y2)
     {
         constexpr int q = Prec<F64>::kNormals;
         const Block b = philox10(0x80000000u + m / q, pctr, sctr, P.pid, P.key0, P.key1);
@@ -568,10 +614,10 @@ struct Walker {
     // reach (as if none ended the walk) and, with a grid, loads the grid
     // density at each, all loads issued before the first is used.  Points past
     // the walk's end are never used.
-    template <int MACRO = Prec<F64>::kMacro>
     __device__ __forceinline__ void advance(const LaneProblem<F64>& P, const typename Prec<F64>::Src& src, T* z,
                                             T* g) const
     {
+        constexpr int MACRO = Prec<F64>::kMacro;
         T p0 = x0, p1 = x1, p2 = x2;
 #pragma unroll
         for (int s = 0; s < MACRO; ++s) {
@@ -631,24 +677,10 @@ struct Walker {
     // the macro-step's last point only when the walk goes on, so a walk that
     // ended keeps them at the macro-step's start (finish recovers the step's
     // two ends from x and y).  g holds the grid density at each point.
-    // The source's density at y: the grid value g, then the analytic bodies
-    // in their order.  With HELD the first prism comes from hq (registers;
-    // lo = +inf when the source has none) and the rest from the source.
-    template <bool HELD>
-    __device__ __forceinline__ static T density(const typename Prec<F64>::Src& src, const T* hq, T g, T y0, T y1, T y2)
-    {
-        if constexpr (HELD) {
-            const bool in = (y0 >= hq[0]) & (y0 < hq[3]) & (y1 >= hq[1]) & (y1 < hq[4]) & (y2 >= hq[2]) & (y2 < hq[5]);
-            return Prec<F64>::bodies(src, in ? g + hq[6] : g, y0, y1, y2, 1);
-        } else {
-            return Prec<F64>::bodies(src, g, y0, y1, y2);
-        }
-    }
-
-    template <bool HELD = false, int MACRO = Prec<F64>::kMacro>
     __device__ __forceinline__ bool steps(const LaneProblem<F64>& P, const typename Prec<F64>::Src& src, const T* y,
-                                          const T* g, int& at, int& how, const T* hq = nullptr)
+                                          const T* g, int& at, int& how)
     {
+        constexpr int MACRO = Prec<F64>::kMacro;
         bool done = false;
         T r = rp;   // the density at the step's start
         if constexpr (!ADJ && loop_exit(LOOP) < 2) {
@@ -662,7 +694,7 @@ struct Walker {
 #pragma unroll
             for (int s = 0; s < MACRO; ++s) {
                 T d2;
-                rn[s] = density<HELD>(src, hq, g[s], y[3 * s], y[3 * s + 1], y[3 * s + 2]);
+                rn[s] = Prec<F64>::bodies(src, g[s], y[3 * s], y[3 * s + 1], y[3 * s + 2]);
                 out[s] = leaves(P, y[3 * s], y[3 * s + 1], y[3 * s + 2], d2);
                 end = end | out[s];
             }
@@ -698,7 +730,7 @@ struct Walker {
                 const T y0 = y[3 * s], y1 = y[3 * s + 1], y2 = y[3 * s + 2];
                 T rn = T(0);
                 if (!ADJ) {
-                    rn = density<HELD>(src, hq, g[s], y0, y1, y2);
+                    rn = Prec<F64>::bodies(src, g[s], y0, y1, y2);
                     add_trapezoid(r, rn);
                 }
                 n += 1;
@@ -709,7 +741,7 @@ struct Walker {
                     const bool deep_y = deep_inside(P, y0, y1, y2, d2);
                     if (!(deep && deep_y)) {
                         const T p0 = s ? y[3 * s - 3] : x0, p1 = s ? y[3 * s - 2] : x1, p2 = s ? y[3 * s - 1] : x2;
-                        stop = bridge_stop(P, n - 1, p0, p1, p2, y0, y1, y2);
+                        stop = bridge_stop(P, pctr, sctr, n - 1, p0, p1, p2, y0, y1, y2);
                     }
                     deep = deep_y;
                 }
@@ -735,13 +767,12 @@ struct Walker {
         return done;
     }
 
-    // Stores the walk's exit record (or flushes its scatter) and frees the
-    // lane.  y holds the macro-step's points (advance) and the walk ended at
-    // step at of them: the end point is y[at], the last point inside the one
-    // before it (x for the first step).
-    template <int MACRO = Prec<F64>::kMacro>
+    // Ends the walk: y holds the macro-step's points (advance) and the walk
+    // ended at step at of them: the end point is y[at], the last point inside
+    // the one before it (x for the first step).
     __device__ __forceinline__ void finish(const LaneProblem<F64>& P, const T* y, int at, int how)
     {
+        constexpr int MACRO = Prec<F64>::kMacro;
         T a0 = x0, a1 = x1, a2 = x2, e0 = y[0], e1 = y[1], e2 = y[2];
 #pragma unroll
         for (int s = 1; s < MACRO; ++s) {
@@ -754,6 +785,13 @@ struct Walker {
                 e2 = y[3 * s + 2];
             }
         }
+        finish_at(P, a0, a1, a2, e0, e1, e2, how);
+    }
+
+    // Stores the exit record (or flushes the scatter) of a walk whose last
+    // step went from a to e, and frees the lane.
+    __device__ __forceinline__ void finish_at(const LaneProblem<F64>& P, T a0, T a1, T a2, T e0, T e1, T e2, int how)
+    {
         const bool capped = how == 1;
         if (ADJ) {
             sc.flush();
@@ -795,6 +833,215 @@ struct Walker {
 };
 
 // ---------------------------------------------------------------------------
+// Shared drain rounds.  A lone walk stepping in its own lane issues every
+// instruction of a step -- some 60 of them, 5 cycles each with one wavefront
+// per SIMD -- for one step's worth of work.  Of a step only the move
+// x + sqrt(dt) z and the trapezoid sum depend on the step before; densities
+// and exit tests do not.  So in a round with at most kCoopLive live walks
+//   1. the chain of moves runs in three lanes per walk, one per axis, each
+//      replacing its normals in LDS by the positions they lead to;
+//   2. all 64 lanes take densities and exit tests of the round's points, up
+//      to MACRO points each, all grid loads in flight together;
+//   3. the lane that holds a walk adds its trapezoid terms in step order, up
+//      to the first point that ends it (nothing to add when every density of
+//      the round is zero).
+// The arithmetic of every step and its order are those of a macro-step, so a
+// walk's record does not depend on the rounds it ran in.
+// With more live walks step 1 would need more than a wavefront's lanes, and
+// the live lanes step through the buffer themselves.
+// Measured with the even shares of Queue::cap, before -> after: 8 stations x
+// 250 walks in FP64 1329 -> 229 us (a call returning host arrays); Table 1's
+// cells Delta t = 0.01, N = 5120: 6.67 -> 4.24 ms, and 0.001, N = 25600:
+// 129 -> 106 ms; its g_z with the bridge test, mixed, N = 2048: 7.17 -> 2.90 ms.
+constexpr int kCoopLive = 21;     // 3 lanes per walk
+
+template <bool F64>
+struct CoopRound {
+    typename Prec<F64>::T dens[64 * Prec<F64>::kMacro];   // density at step s of walk w: dens[s * m + w]
+    int end[kCoopLive + 1];                               // first step that ends walk w
+    int how[kCoopLive + 1];                               // and how (Walker::steps)
+};
+
+// One shared round: m live walks (walk w is held by lane lanes[w]; rank is w
+// in the lanes that hold one), `macros` macro-steps each, whose normals are
+// in zb (normal e of walk w at ((e / NPB) * m + w) * NPB + e % NPB).  P is the
+// live walks' problem.
+template <bool F64, bool KAHAN, int LOOP>
+__device__ __forceinline__ void coop_round(Walker<F64, KAHAN, false, LOOP>& W, const LaneProblem<F64>& P,
+                                           const typename Prec<F64>::Src& src, typename Prec<F64>::T* zb,
+                                           CoopRound<F64>& R, const int* lanes, int m, int macros, int rank)
+{
+    using T = typename Prec<F64>::T;
+    constexpr int NPB = Prec<F64>::kNormals;
+    constexpr int MACRO = Prec<F64>::kMacro;
+    const int lane = (int)__lane_id();
+    const int L = macros * MACRO;                 // steps per walk
+    const int over = 65536 / m + 1;               // t / m = t * over >> 16 for t < 256
+    auto at = [&](int s, int c, int w) {
+        const int e = 3 * s + c;
+        return ((e / NPB) * m + w) * NPB + e % NPB;
+    };
+
+    // 1. positions: lane c m + w moves axis c of walk w
+    {
+        const int c = (lane * over) >> 16, w = lane - c * m;
+        const int from = lanes[w];
+        const T q0 = __shfl(W.x0, from), q1 = __shfl(W.x1, from), q2 = __shfl(W.x2, from);
+        if (c < 3) {
+            T p = c == 0 ? q0 : c == 1 ? q1 : q2;
+            int off[MACRO];
+#pragma unroll
+            for (int i = 0; i < MACRO; ++i) off[i] = at(i, c, w);
+            const int stride = 3 * m * NPB;       // a macro-step's normals
+            constexpr int J = 8 / MACRO;          // macro-steps per batch of 8 steps
+            T z[8];
+            int j = 0;
+            if (J <= macros) {
+#pragma unroll
+                for (int i = 0; i < 8; ++i) z[i] = zb[off[i % MACRO] + (i / MACRO) * stride];
+            }
+            for (; j + J <= macros; j += J) {
+                // the next batch's loads are in flight while this one's chain runs
+                T zn[8] = {};
+                if (j + 2 * J <= macros) {
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) zn[i] = zb[off[i % MACRO] + (j + J + i / MACRO) * stride];
+                }
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    p = Prec<F64>::fmat(P.sdt, z[i], p);
+                    zb[off[i % MACRO] + (j + i / MACRO) * stride] = p;
+                }
+#pragma unroll
+                for (int i = 0; i < 8; ++i) z[i] = zn[i];
+            }
+            for (; j < macros; ++j)
+#pragma unroll
+                for (int i = 0; i < MACRO; ++i) {
+                    const int o = off[i] + j * stride;
+                    p = Prec<F64>::fmat(P.sdt, zb[o], p);
+                    zb[o] = p;
+                }
+        }
+        if (lane < m) R.end[lane] = L;
+    }
+    wave_sync_lds();
+
+    // 2. densities and exit tests: point t = s m + w in lane t mod 64
+    T y[3 * MACRO], g[MACRO];
+#pragma unroll
+    for (int i = 0; i < MACRO; ++i) {
+        int t = lane + 64 * i;
+        if (t >= L * m) t = lane < m ? lane : 0;  // no point: any other
+        const int s = (t * over) >> 16, w = t - s * m;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) y[3 * i + c] = zb[at(s, c, w)];
+        g[i] = T(0);
+    }
+    if (loop_grid(LOOP) && src.has_grid) {
+        GridProbe pr[MACRO];
+#pragma unroll
+        for (int i = 0; i < MACRO; ++i)
+            pr[i] = Prec<F64>::template grid_fetch<loop_levels(LOOP)>(src, y[3 * i], y[3 * i + 1], y[3 * i + 2]);
+#pragma unroll
+        for (int i = 0; i < MACRO; ++i) g[i] = Prec<F64>::template grid_keep<loop_levels(LOOP)>(src, pr[i]);
+    }
+    bool some = false, mass = false;
+    uint32_t ends = 0;                            // bit i: point i ends its walk
+    int hows[MACRO];
+#pragma unroll
+    for (int i = 0; i < MACRO; ++i) {
+        const int t = lane + 64 * i;
+        const bool valid = t < L * m;
+        const int s = (t * over) >> 16, w = valid ? t - s * m : 0;
+        const int from = lanes[w];
+        const uint32_t nw = (uint32_t)__shfl((int)W.n, from);
+        const T y0 = y[3 * i], y1 = y[3 * i + 1], y2 = y[3 * i + 2];
+        const T rn = Prec<F64>::bodies(src, g[i], y0, y1, y2);
+        if (valid) R.dens[t] = rn;
+        mass = mass | (valid & !(rn == T(0)));
+        T d2;
+        const bool out = Walker<F64, KAHAN, false, LOOP>::leaves(P, y0, y1, y2, d2);
+        int stop = -1;
+        if constexpr (loop_exit(LOOP) == 2) {
+            const uint32_t pw = (uint32_t)__shfl((int)W.pctr, from), sw = (uint32_t)__shfl((int)W.sctr, from);
+            T a0 = __shfl(W.x0, from), a1 = __shfl(W.x1, from), a2 = __shfl(W.x2, from);
+            if (P.bridge && valid && !out) {
+                if (s > 0) {
+                    a0 = zb[at(s - 1, 0, w)];
+                    a1 = zb[at(s - 1, 1, w)];
+                    a2 = zb[at(s - 1, 2, w)];
+                }
+                const T da = P.ball ? dist2(a0, a1, a2, P.lo0, P.lo1, P.lo2) : T(0);
+                if (!(W.deep_inside(P, a0, a1, a2, da) && W.deep_inside(P, y0, y1, y2, d2)))
+                    stop = W.bridge_stop(P, pw, sw, nw + (uint32_t)s, a0, a1, a2, y0, y1, y2);
+            }
+        }
+        const bool end = valid & (out | (stop >= 0) | ((int64_t)nw + s + 1 >= P.max_steps));
+        hows[i] = out ? 0 : stop >= 0 ? 2 + stop : 1;
+        if (end) {
+            atomicMin(&R.end[w], s);
+            ends |= 1u << i;
+        }
+        some = some | end;
+    }
+    const bool any_mass = __ballot(mass | (W.active & !(W.rp == T(0)))) != 0ull;
+    const bool any_end = __ballot(some) != 0ull;
+    wave_sync_lds();
+    if (any_end) {
+#pragma unroll
+        for (int i = 0; i < MACRO; ++i) {
+            if (ends & (1u << i)) {
+                const int t = lane + 64 * i;
+                const int s = (t * over) >> 16, w = t - s * m;
+                if (R.end[w] == s) R.how[w] = hows[i];
+            }
+        }
+        wave_sync_lds();
+    }
+
+    // 3. the walks' sums and ends
+    if (W.active) {
+        const int f = any_end ? R.end[rank] : L;
+        const int taken = f < L ? f + 1 : L;
+        // a sum of zeros leaves an uncompensated sum as it is
+        if (KAHAN || any_mass) {
+            T r = W.rp;
+            for (int s = 0; s < taken; s += 8) {
+                T d[8];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) d[i] = R.dens[(s + i < L ? s + i : L - 1) * m + rank];
+#pragma unroll
+                for (int i = 0; i < 8; ++i)
+                    if (s + i < taken) {
+                        W.add_trapezoid(r, d[i]);
+                        r = d[i];
+                    }
+            }
+            W.rp = r;
+        }
+        W.n += (uint32_t)taken;
+        W.k += (uint32_t)(3 * macros);
+        const int l = f < L ? f : L - 1;          // the last point reached
+        const T e0 = zb[at(l, 0, rank)], e1 = zb[at(l, 1, rank)], e2 = zb[at(l, 2, rank)];
+        if (f < L) {
+            T a0 = W.x0, a1 = W.x1, a2 = W.x2;
+            if (f > 0) {
+                a0 = zb[at(f - 1, 0, rank)];
+                a1 = zb[at(f - 1, 1, rank)];
+                a2 = zb[at(f - 1, 2, rank)];
+            }
+            W.finish_at(P, a0, a1, a2, e0, e1, e2, R.how[rank]);
+        } else {
+            W.x0 = e0;
+            W.x1 = e1;
+            W.x2 = e2;
+            W.deep = false;                       // tested again where it matters
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------
 // The kernel body.
 // ---------------------------------------------------------------------------
 // DENSE (adjoint only): blocks of kAdjDenseBlock threads with a dense
@@ -820,6 +1067,7 @@ __device__ __forceinline__ void walk_body(const Args& A)
 
     __shared__ int tail_lane[TAIL_WAVES][64];
     __shared__ T tail_z[TAIL_WAVES][3 * 64][NPB];
+    __shared__ CoopRound<F64> coop[DRAIN && !ADJ ? kMaxWaves : 1];
     const BmTables* bmt = nullptr;
     if constexpr (F64) {
         BmTables* t = bm_tables();
@@ -830,7 +1078,7 @@ __device__ __forceinline__ void walk_body(const Args& A)
     Queue Q;
     LaneProblem<F64> P;
     if constexpr (BATCH) {
-        Q = Queue{A.queue, (uint64_t)A.n_tasks, (uint32_t)A.grab, A.total_waves, A.stripes, A.refill_cost};
+        Q = Queue{A.queue, (uint64_t)A.n_tasks, (uint32_t)A.grab, A.total_waves, A.stripes, A.refill_cost, A.cap};
         P.C = nullptr;
         P.src = nullptr;
         P.sdt = T(0);
@@ -844,7 +1092,7 @@ __device__ __forceinline__ void walk_body(const Args& A)
         P.max_steps = 0;
     } else {
         Q = Queue{A.c.queue, (uint64_t)A.c.n_tasks, (uint32_t)A.c.grab, A.c.total_waves, A.c.stripes,
-                  A.c.refill_cost};
+                  A.c.refill_cost, A.c.cap};
         P.load(A.c, A.src);
         // held in vector registers, as a batch holds them: kept in scalar
         // registers beside the source's bodies they overflow the scalar file,
@@ -886,10 +1134,6 @@ __device__ __forceinline__ void walk_body(const Args& A)
             f(source());
         }
     };
-    // drain rounds hold the first prism in registers (below); not in grid
-    // loops, whose sources are mostly grids, nor in FP64 batches, whose
-    // registers it costs more than it gains (both measured)
-    constexpr bool kHeld = !loop_grid(LOOP) && !(F64 && BATCH);
     Pool pool = start_pool(Q);
     Walker<F64, KAHAN, ADJ, LOOP, DENSE> W;
     W.active = false;
@@ -930,9 +1174,8 @@ __device__ __forceinline__ void walk_body(const Args& A)
     uint64_t task_base = 0;   // task of queue index 0
     if constexpr (!BATCH) task_base = (uint64_t)A.c.task0;
 
-    // The wavefront's walks until its queue is used up and they are done.
-    auto run_waves = [&]() {
-    for (;;) {
+    // Fills the wavefront's free lanes with walks from the queue.
+    auto start_walks = [&]() {
         const uint64_t got = refill(pool, Q, W.active);
         if (got != ~0ull) {
             const WalkCommon* Cp;
@@ -996,27 +1239,61 @@ __device__ __forceinline__ void walk_body(const Args& A)
                 W.active = true;
             }
         }
-        const uint64_t live = __ballot(W.active);
-        if (live == 0ull) {
-            if (pool.exhausted) break;
-            continue;
-        }
-        const int m = __popcll(live);
+    };
 
-        if (DRAIN && pool.exhausted) {
-            // ---- drain round: the queue is empty, so every lane generates
-            // three Philox blocks for the live walks of its wavefront (block
-            // slot g = r * m + w holds block r of live walk w), and each live
-            // walk then takes 2 * 64/m (FP64) or 4 * 64/m (mixed) steps from
-            // LDS.  With m = 64 this costs what a macro-step costs; with few
-            // live walks it spreads their random-number generation over all
-            // lanes instead of leaving most lanes idle.
+    // The wavefront's walks until its queue is used up and they are done: in
+    // macro-steps while there are walks to refill its lanes with, then in
+    // drain rounds.  (Two loops, so that what the drain rounds keep in
+    // registers is not live through the macro-steps.)
+    auto run_waves = [&]() {
+        while (!DRAIN || Q.cap == 64u) {
+            start_walks();
+            if (__ballot(W.active) == 0ull) {
+                if (pool.exhausted) break;
+                continue;
+            }
+            if (DRAIN && pool.exhausted) break;
+            if (!W.active) continue;
+
+            // ---- macro-step: 3 blocks of this lane's own walk ----
+            T z[3 * NPB];
+#pragma unroll
+            for (int b = 0; b < 3; ++b) {
+                const Block bl = philox10(W.k + b, W.pctr, W.sctr, P.pid, P.key0, P.key1);
+                Prec<F64>::normals(bl, z + NPB * b, bmt);
+            }
+            W.k += 3;
+            bool done = false;
+            int how = 0, at = 0;
+            with_source([&](const typename Prec<F64>::Src& src) {
+                T g[MACRO];
+                W.advance(P, src, z, g);
+                done = W.steps(P, src, z, g, at, how);
+            });
+            if (done) W.finish(P, z, at, how);
+        }
+        while (DRAIN) {
+            if (!pool.exhausted) start_walks();      // a capped launch
+            const uint64_t live = __ballot(W.active);
+            if (live == 0ull) {
+                if (pool.exhausted) break;
+                continue;
+            }
+            const int m = __popcll(live);
+            // ---- drain round: the queue is empty, or the launch gives no
+            // wavefront more walks than these, so every lane generates Philox
+            // blocks for the live walks of its wavefront (block slot
+            // g = r * m + w holds block r of live walk w): 192 slots, or 128
+            // where 33 to 42 live walks would leave a third of them unused.
+            // Each live walk then takes B / 3 macro-steps from LDS.
             const int rank = __popcll(live & __lanemask_lt());
             if (W.active) tail_lane[wave][rank] = lane;
             wave_sync_lds();
-            const int B = 3 * (64 / m);                // blocks per live walk this round
+            const int macros = m > 32 ? 1 : 64 / m;    // macro-steps per live walk this round
+            const int B = 3 * macros;                  // blocks per live walk
+            const int passes = m > 32 && m <= 42 ? 2 : 3;
 #pragma unroll 1
-            for (int i = 0; i < 3; ++i) {
+            for (int i = 0; i < passes; ++i) {
                 const int g = lane + 64 * i;
                 const int w = g % m;
                 const int r = g / m;
@@ -1041,97 +1318,54 @@ __device__ __forceinline__ void walk_body(const Args& A)
                 }
             }
             wave_sync_lds();
+            if constexpr (!ADJ) {
+                if (m <= kCoopLive) {
+                    // the problem of the first live walk; the round is shared
+                    // only when all live walks belong to it
+                    const int first = __ffsll((unsigned long long)live) - 1;
+                    LaneProblem<F64> PE = P;
+                    bool same = true;
+                    if constexpr (BATCH) {
+                        const uint64_t pc = lane_u64((uint64_t)P.C, first);
+                        same = __ballot(W.active && (uint64_t)P.C != pc) == 0ull;
+                        if (same) PE.from_lane(P, first, !UKEY);
+                    }
+                    if (same) {
+                        const typename Prec<F64>::Src* sp;
+                        if constexpr (BATCH && !SHARED)
+                            sp = (const typename Prec<F64>::Src*)(const __attribute__((address_space(4)))
+                                                                  typename Prec<F64>::Src*)(uint64_t)PE.src;
+                        else
+                            sp = &source();
+                        coop_round(W, PE, *sp, &tail_z[wave][0][0], coop[wave], tail_lane[wave], m, macros, rank);
+                        wave_sync_lds();
+                        continue;
+                    }
+                }
+            }
             if (W.active) {
-                const int n_steps = B * NPB / 3;      // a multiple of MACRO
+                const int n_steps = MACRO * macros;
                 bool done = false;
                 int how = 0;
-                if constexpr (kHeld) {
-                    // A walk stepping alone here has no other wavefronts to
-                    // hide the latency of re-reading the source's bodies at
-                    // every step: the first prism is held in registers for
-                    // the round.
-                    with_source([&](const typename Prec<F64>::Src& src) {
-                        const bool any = src.n_prisms > 0;
-                        T hq[7];
+                for (int s0 = 0; s0 < n_steps && !done; s0 += MACRO) {
+                    T zz[3 * MACRO];
 #pragma unroll
-                        for (int c = 0; c < 7; ++c)
-                            hq[c] = in_vgpr(any ? (T)src.prisms[0][c] : (c == 0 ? (T)__builtin_inf() : T(0)));
-                        // FP64: two macro-steps at a time while the round has
-                        // them, so that their densities and exit tests overlap
-                        // (mixed walks measured slower so: registers)
-                        constexpr int DRAIN = F64 ? 2 * MACRO : MACRO;
-                        int s0 = 0;
-                        for (; s0 + DRAIN <= n_steps && !done; s0 += DRAIN) {
-                            T zz[3 * DRAIN];
-#pragma unroll
-                            for (int c = 0; c < 3 * DRAIN; ++c) {
-                                const int q = 3 * s0 + c;
-                                zz[c] = tail_z[wave][(q / NPB) * m + rank][q % NPB];
-                            }
-                            int at = 0;
-                            T g[DRAIN];
-                            W.template advance<DRAIN>(P, src, zz, g);
-                            done = W.template steps<true, DRAIN>(P, src, zz, g, at, how, hq);
-                            if (done) W.template finish<DRAIN>(P, zz, at, how);
-                        }
-                        if constexpr (DRAIN != MACRO) {
-                            for (; s0 < n_steps && !done; s0 += MACRO) {
-                                T zz[3 * MACRO];
-#pragma unroll
-                                for (int c = 0; c < 3 * MACRO; ++c) {
-                                    const int q = 3 * s0 + c;
-                                    zz[c] = tail_z[wave][(q / NPB) * m + rank][q % NPB];
-                                }
-                                int at = 0;
-                                T g[MACRO];
-                                W.advance(P, src, zz, g);
-                                done = W.template steps<true>(P, src, zz, g, at, how, hq);
-                                if (done) W.finish(P, zz, at, how);
-                            }
-                        }
-                    });
-                } else {
-                    for (int s0 = 0; s0 < n_steps && !done; s0 += MACRO) {
-                        T zz[3 * MACRO];
-#pragma unroll
-                        for (int c = 0; c < 3 * MACRO; ++c) {
-                            const int q = 3 * s0 + c;
-                            zz[c] = tail_z[wave][(q / NPB) * m + rank][q % NPB];
-                        }
-                        int at = 0;
-                        with_source([&](const typename Prec<F64>::Src& src) {
-                            T g[MACRO];
-                            W.advance(P, src, zz, g);
-                            done = W.steps(P, src, zz, g, at, how);
-                        });
-                        if (done) W.finish(P, zz, at, how);
+                    for (int c = 0; c < 3 * MACRO; ++c) {
+                        const int q = 3 * s0 + c;
+                        zz[c] = tail_z[wave][(q / NPB) * m + rank][q % NPB];
                     }
+                    int at = 0;
+                    with_source([&](const typename Prec<F64>::Src& src) {
+                        T g[MACRO];
+                        W.advance(P, src, zz, g);
+                        done = W.steps(P, src, zz, g, at, how);
+                    });
+                    if (done) W.finish(P, zz, at, how);
                 }
                 W.k += (uint32_t)B;
             }
             wave_sync_lds();
-            continue;
         }
-
-        if (!W.active) continue;
-
-        // ---- macro-step: 3 blocks of this lane's own walk ----
-        T z[3 * NPB];
-#pragma unroll
-        for (int b = 0; b < 3; ++b) {
-            const Block bl = philox10(W.k + b, W.pctr, W.sctr, P.pid, P.key0, P.key1);
-            Prec<F64>::normals(bl, z + NPB * b, bmt);
-        }
-        W.k += 3;
-        bool done = false;
-        int how = 0, at = 0;
-        with_source([&](const typename Prec<F64>::Src& src) {
-            T g[MACRO];
-            W.advance(P, src, z, g);
-            done = W.steps(P, src, z, g, at, how);
-        });
-        if (done) W.finish(P, z, at, how);
-    }
     };
 
     if constexpr (DENSE) {
@@ -1146,7 +1380,7 @@ __device__ __forceinline__ void walk_body(const Args& A)
         for (;;) {
             const int s = next_station;
             if (s < 0) break;
-            Q = Queue{A.c.queue + s, per, (uint32_t)A.c.grab, waves_per_station, 1u, A.c.refill_cost};
+            Q = Queue{A.c.queue + s, per, (uint32_t)A.c.grab, waves_per_station, 1u, A.c.refill_cost, 64u};
             pool = start_pool(Q);
             task_base = (uint64_t)s * per;
             run_waves();
@@ -1295,22 +1529,28 @@ template <bool F64, bool KAHAN, bool ADJ, class A>
 void launch_walk(const A& a, int loop, const LaunchCfg& cfg, hipStream_t stream, bool dense)
 {
     with_loop(ADJ ? loop_exit(loop) : loop, [&](auto L) {
-        if (ADJ && dense)
-            hipLaunchKernelGGL((adjoint_dense_kernel<F64, KAHAN, loop_exit(decltype(L)::value)>), dim3(cfg.grid),
-                               dim3(cfg.block), 0, stream, a);
-        else
-            hipLaunchKernelGGL((walk_kernel<F64, KAHAN, ADJ, decltype(L)::value>), dim3(cfg.grid), dim3(cfg.block),
-                               0, stream, a);
+        constexpr int LOOP = ADJ ? loop_exit(decltype(L)::value) : decltype(L)::value;
+        if constexpr (ADJ) {
+            if (dense) {
+                hipLaunchKernelGGL((adjoint_dense_kernel<F64, KAHAN, LOOP>), dim3(cfg.grid), dim3(cfg.block), 0, stream,
+                                   a);
+                return;
+            }
+        }
+        hipLaunchKernelGGL((walk_kernel<F64, KAHAN, ADJ, LOOP>), dim3(cfg.grid), dim3(cfg.block), 0, stream, a);
     });
 }
 
-template <int LOOP, bool ADJ>
+template <int VARIANT, bool ADJ>
 const void* walk_fn(int precision, bool dense)
 {
-    if (ADJ && dense)
-        return precision == FK_F64 ? (const void*)adjoint_dense_kernel<true, false, loop_exit(LOOP)>
-             : precision == FK_MIXED_KAHAN ? (const void*)adjoint_dense_kernel<false, true, loop_exit(LOOP)>
-                                           : (const void*)adjoint_dense_kernel<false, false, loop_exit(LOOP)>;
+    constexpr int LOOP = ADJ ? loop_exit(VARIANT) : VARIANT;
+    if constexpr (ADJ) {
+        if (dense)
+            return precision == FK_F64 ? (const void*)adjoint_dense_kernel<true, false, LOOP>
+                 : precision == FK_MIXED_KAHAN ? (const void*)adjoint_dense_kernel<false, true, LOOP>
+                                               : (const void*)adjoint_dense_kernel<false, false, LOOP>;
+    }
     return precision == FK_F64 ? (const void*)walk_kernel<true, false, ADJ, LOOP>
          : precision == FK_MIXED_KAHAN ? (const void*)walk_kernel<false, true, ADJ, LOOP>
                                        : (const void*)walk_kernel<false, false, ADJ, LOOP>;

@@ -98,13 +98,15 @@ __device__ __forceinline__ double neg2_log(double u)
 // correction.  Each step roughly doubles the correct bits of the estimate;
 // with one iteration the Box-Muller normals still agree with a correctly
 // rounded reference to 2e-15 of max(1, |z|), within the 4e-15 the reference
-// angle's own rounding allows.
+// angle's own rounding allows.  At x = +-0 the estimate, infinite there, is
+// replaced by a large finite number, which every product then carries to 0
+// (one minimum instead of a compare and two selects on the result).
 #ifndef FK_SQRT_ITERS
 #define FK_SQRT_ITERS 1
 #endif
 __device__ __forceinline__ double sqrt_nonneg(double x)
 {
-    const double y = __builtin_amdgcn_rsq(x);
+    const double y = fmin(__builtin_amdgcn_rsq(fabs(x)), 0x1p+500);
     double g = x * y, h = 0.5 * y;
 #pragma unroll
     for (int i = 0; i < FK_SQRT_ITERS; ++i) {
@@ -112,8 +114,7 @@ __device__ __forceinline__ double sqrt_nonneg(double x)
         g = fma(g, r, g);
         h = fma(h, r, h);
     }
-    g = fma(fma(-g, g, x), h, g);
-    return x > 0.0 ? g : 0.0;
+    return fma(fma(-g, g, x), h, g);
 }
 
 // sin and cos of 2 pi u for u in (0, 1].  x = 2u is reduced exactly to
@@ -157,15 +158,21 @@ __device__ __forceinline__ void sincos_2pi(double u, double& s, double& c)
 // LDS and filled at the start of every launch by the table-free routines
 // above (so they carry those routines' ~1 ulp accuracy):
 //   sc[k] = (sin, cos)(2 pi k / 256), k = 0..255;
-//   lg[j] = (v, -ln v) with v = 1/c rounded, c = 1 + (j - 37)/128, j = 0..90,
-//           the grid of c over [sqrt(1/2), sqrt(2)).
+//   lg[j] = (v, 2 ln v), v = 1/c rounded, c the middle of interval j of the
+//           128 that [0.709, 1.418) is cut into (neg2_log_t); c = 1 is one.
 struct BmTables {
     static constexpr int kSc = 256;
-    static constexpr int kLg = 91;
-    static constexpr int kLgOff = 37;
+    static constexpr int kLg = 128;
+    static constexpr uint32_t kLgLow = 0x3fe6b000u;   // high word of the range's lower end
+    static constexpr int kLgShift = 13;               // an interval is 2^13 high words wide
+    // the interval next below that of 1, where 2 ln v and the series cancel
+    // most: its v lies within 5e-7 of 1/c and has 2 ln v a double to 1e-5 ulp
+    static constexpr uint32_t kLgBelow1 = ((0x3ff00000u - kLgLow) >> kLgShift) - 1u;
     double2 sc[kSc];
     double2 lg[kLg];
 };
+static_assert((0x3ff00000u - BmTables::kLgLow) % (1u << BmTables::kLgShift) == 1u << (BmTables::kLgShift - 1),
+              "1.0 must be the middle of an interval");
 
 // The block's table, in LDS (one instance per kernel that uses it).
 __device__ __forceinline__ BmTables* bm_tables()
@@ -183,29 +190,31 @@ __device__ __forceinline__ void fill_bm_tables(BmTables& T)
             sincos_2pi((double)i * (1.0 / BmTables::kSc), s, c);
             T.sc[i] = make_double2(s, c);
         } else {
-            const int j = i - BmTables::kSc;
-            const double v = 1.0 / (1.0 + (double)(j - BmTables::kLgOff) * (1.0 / 128.0));
-            T.lg[j] = make_double2(v, 0.5 * neg2_log(v));
+            const uint32_t j = (uint32_t)(i - BmTables::kSc);
+            const uint32_t c = BmTables::kLgLow + (j << BmTables::kLgShift) + (1u << (BmTables::kLgShift - 1));
+            const double v = 1.0 / __hiloint2double((int)c, 0);
+            T.lg[j] = j == BmTables::kLgBelow1 ? make_double2(0x1.010108c28b78cp+0, 0x1.00880f5e5822bp-7)
+                                               : make_double2(v, -neg2_log(v));
         }
     }
     __syncthreads();
 }
 
-// -2 ln u for u in (0, 1] with the table: u = m 2^e, m in [sqrt(1/2),
-// sqrt(2)); c = 1 + j/128 the nearest grid point, v = 1/c rounded; then
-// ln m = -ln v + ln(1 + r) with r = m v - 1 (one rounding, |r| < 0.0056), and
-// ln(1 + r) is its series to r^7 (truncation below 2.2e-17 relative).  Near
-// u = 1 the grid point is c = v = 1 and r = m - 1 exactly.
+// -2 ln u for a positive normal u with the table (Tang's table-driven
+// logarithm, 1990).  u = m 2^k with m in [0.709, 1.418): k and m's interval
+// come from the high word of u by integer operations (half the cost of
+// frexp, a compare and a rounded conversion: 12 issue cycles instead of 48).
+// With c the interval's middle and v = 1/c rounded, ln m = -ln v + ln(1 + r),
+// r = m v - 1 (one rounding, |r| < 0.0040), and ln(1 + r) is its series to
+// r^7 (truncation below 3e-18 relative).  Near u = 1 the middle is c = v = 1
+// and r = m - 1 exactly.
 __device__ __forceinline__ double neg2_log_t(double u, const BmTables& T)
 {
-    double m = __builtin_amdgcn_frexp_mant(u);   // [0.5, 1)
-    int e = __builtin_amdgcn_frexp_exp(u);
-    if (m < 0x1.6a09e667f3bcdp-1) {
-        m = 2.0 * m;
-        e -= 1;
-    }
-    const int j = (int)__builtin_rint((m - 1.0) * 128.0) + BmTables::kLgOff;   // both exact
-    const double2 g = T.lg[j];
+    const uint32_t hw = (uint32_t)__double2hiint(u);
+    const uint32_t t = hw - BmTables::kLgLow;
+    const int k = (int)t >> 20;
+    const double m = __hiloint2double((int)(hw - (t & 0xfff00000u)), __double2loint(u));
+    const double2 g = T.lg[(t >> BmTables::kLgShift) & (BmTables::kLg - 1)];
     const double r = fma(m, g.x, -1.0);
     double p = 0x1.2492492492492p-3;             // 1/7
     p = fma(p, r, -0x1.5555555555555p-3);        // -1/6
@@ -214,49 +223,57 @@ __device__ __forceinline__ double neg2_log_t(double u, const BmTables& T)
     p = fma(p, r, 0x1.5555555555555p-2);         // 1/3
     p = fma(p, r, -0.5);
     const double l1p = fma(p, r * r, r);         // ln(1 + r)
-    const double fe = -2.0 * (double)e;
-    return fma(fe, 0x1.62e42fee00000p-1, fma(fe, 0x1.a39ef35793c76p-33, -2.0 * (g.y + l1p)));
+    const double fk = (double)k;
+    return fma(fk, -0x1.62e42fee00000p+0, fma(fk, -0x1.a39ef35793c76p-32, fma(-2.0, l1p, g.y)));
 }
 
-// sin and cos of 2 pi u, u in (0, 1], with the table: k = nearest integer
-// to 256 u, t = u - k/256 (exact, |t| <= 1/512), theta = 2 pi t; sin and cos
-// of theta by their series to theta^7 and theta^6 (truncation below 7e-18
+// sin and cos of 2 pi (k/256 + t), |t| <= 1/512, with the table: sin and cos
+// of 2 pi t by their series in t to t^7 and t^6 (truncation below 7e-18
 // relative and 2e-20 absolute), rotated by the table's angle 2 pi k / 256.
-__device__ __forceinline__ void sincos_2pi_t(double u, const BmTables& T, double& s, double& c)
+__device__ __forceinline__ void sincos_2pi_t(uint32_t k, double t, const BmTables& T, double& s, double& c)
 {
-    const double q = __builtin_rint(256.0 * u);
-    const double t = fma(-q, 1.0 / 256.0, u);
-    const double th = t * 0x1.921fb54442d18p+2;  // 2 pi
-    const double z = th * th;
-    double ps = fma(-0x1.a01a01a01a01ap-13, z, 0x1.1111111111111p-7);   // -1/5040, 1/120
-    ps = fma(ps, z, -0x1.5555555555555p-3);                              // -1/6
-    const double st = fma(th * z, ps, th);
-    double pc = fma(-0x1.6c16c16c16c17p-10, z, 0x1.5555555555555p-5);  // -1/720, 1/24
-    pc = fma(pc, z, -0.5);
+    const double z = t * t;
+    double ps = fma(-0x1.32d2cce62bd86p+6, z, 0x1.466bc6775aae2p+6);    // -(2 pi)^7/7!, (2 pi)^5/5!
+    ps = fma(ps, z, -0x1.4abbce625be53p+5);                              // -(2 pi)^3/3!
+    const double st = t * fma(ps, z, 0x1.921fb54442d18p+2);              // 2 pi
+    double pc = fma(-0x1.55d3c7e3cbffap+6, z, 0x1.03c1f081b5ac4p+6);    // -(2 pi)^6/6!, (2 pi)^4/4!
+    pc = fma(pc, z, -0x1.3bd3cc9be45dep+4);                              // -(2 pi)^2/2!
     const double ct = fma(pc, z, 1.0);
-    const double2 a = T.sc[(int)q & (BmTables::kSc - 1)];
+    const double2 a = T.sc[k];
     s = fma(a.x, ct, a.y * st);
     c = fma(a.y, ct, -(a.x * st));
 }
 
-// FP64 stream: one block -> two 53-bit uniforms in (0, 1] -> one Box-Muller
-// pair (cosine branch first): z0 = R cos(2 pi U2), z1 = R sin(2 pi U2),
-// R = sqrt(-2 ln U1).
-// ((hi << 21 | lo >> 11) + 1) * 2^-53, formed without a 64-bit integer: both
-// terms below are exact doubles and so is their sum (a 53-bit integer times
-// 2^-53), so the one rounding of the fma changes nothing.
+// The FP64 stream's uniform U = (hi << 21 | lo >> 11) + 1) 2^-53 is the sum
+// of hi 2^-32 and (l + 1) 2^-53, l = lo >> 11.  A word placed under a fixed
+// high word is a double offset by a power of two, without a conversion:
+//   high_part(w) = 2^20 + w 2^-32,   low_part(lo) = 0.5 + (l + 1) 2^-53,
+// and the offsets leave in additions that are exact.
+__device__ __forceinline__ double high_part(uint32_t w) { return __hiloint2double(0x41300000, (int)w); }
+__device__ __forceinline__ double low_part(uint32_t lo) { return __hiloint2double(0x3fe00000, (int)((lo >> 11) + 1u)); }
+
 __device__ __forceinline__ double uniform53(uint32_t hi, uint32_t lo)
 {
-    return fma((double)hi, 0x1p-32, (double)((lo >> 11) + 1u) * 0x1p-53);
+    return (high_part(hi) - 0x1.000008p+20) + low_part(lo);             // 2^20 + 1/2
 }
 
+// FP64 stream: one block -> two 53-bit uniforms in (0, 1] -> one Box-Muller
+// pair (cosine branch first): z0 = R cos(2 pi U2), z1 = R sin(2 pi U2),
+// R = sqrt(-2 ln U1).  U2's nearest k/256 and its offset t from it are taken
+// from the words: with x = hi + 2^23, k = x >> 24 (mod 256) and
+// t = (x mod 2^24) 2^-32 - 2^-9 + (l + 1) 2^-53, exactly.
+// Bound by VALU issue: a macro-step's three pairs take 290 VALU instructions
+// with their Philox blocks, 364 when frexp, rounded conversions and ldexp did
+// the reductions.  Before -> after: Table 1's Delta t = 0.001, N = 25600 cell
+// 106 -> 97 ms, the SI-prism u + g_z batch (15001 walks) 129 -> 115 ms, 11
+// voxel models 43.3 -> 40.1 ms, the 32^3 gradient 33.5 -> 30.4 ms.
 __device__ __forceinline__ void normals_f64(const Block& b, const BmTables& T, double& z0, double& z1)
 {
-    const double u1 = uniform53(b.w1, b.w0);
-    const double u2 = uniform53(b.w3, b.w2);
-    const double r = sqrt_nonneg(neg2_log_t(u1, T));
+    const double r = sqrt_nonneg(neg2_log_t(uniform53(b.w1, b.w0), T));
+    const uint32_t x = b.w3 + 0x800000u;
+    const double t = (high_part(x & 0xffffffu) - 0x1.00000808p+20) + low_part(b.w2);   // 2^20 + 1/2 + 2^-9
     double s, co;
-    sincos_2pi_t(u2, T, s, co);
+    sincos_2pi_t(x >> 24, t, T, s, co);
     z0 = r * co;
     z1 = r * s;
 }

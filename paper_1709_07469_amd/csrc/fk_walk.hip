@@ -341,6 +341,17 @@ struct Scatter {
     }
 };
 
+// The launch's one generator key, in scalar registers and opaque from here on:
+// the ten rounds' keys are then scalar additions of every macro-step (the
+// scalar unit is idle) instead of twenty values kept over the whole loop.
+// FP64 walks, whose constants fill the scalar registers, got those back from
+// spill lanes, 18 VALU lane reads a macro-step; mixed walks hold them without
+// spilling and are 1.5 % faster so (the 32-model batch).
+__device__ __forceinline__ void scalar_key(uint32_t& key0, uint32_t& key1)
+{
+    asm volatile("" : "+s"(key0), "+s"(key1));
+}
+
 // ---------------------------------------------------------------------------
 // Precision traits.
 // ---------------------------------------------------------------------------
@@ -1257,9 +1268,11 @@ __device__ __forceinline__ void walk_body(const Args& A)
 
             // ---- macro-step: 3 blocks of this lane's own walk ----
             T z[3 * NPB];
+            uint32_t key0 = P.key0, key1 = P.key1;
+            if constexpr (F64 && (!BATCH || UKEY)) scalar_key(key0, key1);
 #pragma unroll
             for (int b = 0; b < 3; ++b) {
-                const Block bl = philox10(W.k + b, W.pctr, W.sctr, P.pid, P.key0, P.key1);
+                const Block bl = philox10(W.k + b, W.pctr, W.sctr, P.pid, key0, key1);
                 Prec<F64>::normals(bl, z + NPB * b, bmt);
             }
             W.k += 3;
@@ -1302,6 +1315,7 @@ __device__ __forceinline__ void walk_body(const Args& A)
                 const uint32_t ps = (uint32_t)__shfl((int)W.pctr, src);
                 const uint32_t ss = (uint32_t)__shfl((int)W.sctr, src);
                 uint32_t key0 = P.key0, key1 = P.key1, pid = P.pid;
+                if constexpr (F64 && (!BATCH || UKEY)) scalar_key(key0, key1);
                 if constexpr (BATCH) {
                     if constexpr (!UKEY) {
                         key0 = (uint32_t)__shfl((int)P.key0, src);

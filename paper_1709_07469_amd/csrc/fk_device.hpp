@@ -335,24 +335,44 @@ __device__ __forceinline__ int64_t voxel_f64(const SourceF64& s, double x, doubl
     return in ? ((int64_t)(int)tz * s.n[1] + (int)ty) * s.n[0] + (int)tx : -1;
 }
 
-// Density of the analytic bodies at (x, y, z), added to r in body order.
-// The membership tests are combined without short-circuiting and the sum is
-// selected, not branched on: a body's bounds then load together (one wait
-// instead of one per bound) and no lane diverges.
-__device__ __forceinline__ double bodies_f64(const SourceF64& s, double r, double x, double y, double z)
+// Densities of the analytic bodies at N points, added to r[0 .. N - 1] in body
+// order.  A body's bounds are loaded once for all the points and its
+// membership tests combined without short-circuiting, so that they load
+// together (one wait instead of one per bound); nothing is added while no
+// lane has a point inside, which is the usual case far from the bodies.
+// One loop over the bodies per macro-step instead of one per point: SI-prism
+// u + g_z FP64 115 -> 110 ms, g_z Kahan 100 -> 93.5 ms, the 32-model batch
+// (no bodies: the loops' counts are read once) 139.3 -> 136.2 ms.
+template <int N, class Src, class T>
+__device__ __forceinline__ void bodies(const Src& s, const T* y, T* r)
 {
     for (int j = 0; j < s.n_prisms; ++j) {
-        const double* q = s.prisms[j];
-        const bool in = (x >= q[0]) & (x < q[3]) & (y >= q[1]) & (y < q[4]) & (z >= q[2]) & (z < q[5]);
-        r = in ? r + q[6] : r;
+        const T* q = s.prisms[j];
+        bool in[N], some = false;
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            const T y0 = y[3 * i], y1 = y[3 * i + 1], y2 = y[3 * i + 2];
+            in[i] = (y0 >= q[0]) & (y0 < q[3]) & (y1 >= q[1]) & (y1 < q[4]) & (y2 >= q[2]) & (y2 < q[5]);
+            some = some | in[i];
+        }
+        if (__ballot(some) != 0ull)
+#pragma unroll
+            for (int i = 0; i < N; ++i) r[i] = in[i] ? r[i] + q[6] : r[i];
     }
     for (int j = 0; j < s.n_spheres; ++j) {
-        const double* q = s.spheres[j];
-        const double dx = x - q[0], dy = y - q[1], dz = z - q[2];
-        const bool in = dx * dx + dy * dy + dz * dz < q[3] * q[3];
-        r = in ? r + q[4] : r;
+        const T* q = s.spheres[j];
+        const T r2 = q[3] * q[3];
+        bool in[N], some = false;
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            const T dx = y[3 * i] - q[0], dy = y[3 * i + 1] - q[1], dz = y[3 * i + 2] - q[2];
+            in[i] = dx * dx + dy * dy + dz * dz < r2;
+            some = some | in[i];
+        }
+        if (__ballot(some) != 0ull)
+#pragma unroll
+            for (int i = 0; i < N; ++i) r[i] = in[i] ? r[i] + q[4] : r[i];
     }
-    return r;
 }
 
 // A floored coordinate as an int (v_cvt_i32_f64): exact for integers in the
@@ -380,7 +400,7 @@ __device__ __forceinline__ bool in_axis(int i, int n) { return (uint32_t)i < (ui
 // and take bounded steps inside the box).  LEVELS: the grid is given by
 // levels, the voxel's density levels[idx[v]]; fetch loads the level and keep
 // its density (the index grid is a quarter of the FP32 grid's size).
-// grid_in_* need a grid (has_grid); grid_* check for one.
+// Both need a grid (has_grid).
 struct GridProbe {
     float r;      // the voxel's density (FP32 grid)
     uint32_t b;   // or its level (grid by levels)
@@ -437,26 +457,6 @@ __device__ __forceinline__ double grid_keep_f64(const SourceF64& s, const GridPr
     return (double)probe_keep<LEVELS>(s, p);
 }
 
-template <bool LEVELS = false>
-__device__ __forceinline__ double grid_in_f64(const SourceF64& s, double x, double y, double z)
-{
-    return grid_keep_f64<LEVELS>(s, grid_fetch_f64<LEVELS>(s, x, y, z));
-}
-
-// LEVELS: the kernel's grids are given by levels (a compile-time property
-// of the launch, like the stepping loop's lookup).
-template <bool LEVELS = false>
-__device__ __forceinline__ double grid_f64(const SourceF64& s, double x, double y, double z)
-{
-    return s.has_grid ? grid_in_f64<LEVELS>(s, x, y, z) : 0.0;
-}
-
-template <bool LEVELS = false>
-__device__ __forceinline__ double rho_f64(const SourceF64& s, double x, double y, double z)
-{
-    return bodies_f64(s, grid_f64<LEVELS>(s, x, y, z), x, y, z);
-}
-
 // floor(x) as an int in one instruction (v_cvt_flr_i32_f32 rounds toward
 // -infinity while it converts).  Equal to (int)floorf(x) for finite x in the
 // int range; beyond it the result saturates to INT_MIN or INT_MAX, which the
@@ -486,23 +486,7 @@ __device__ __forceinline__ int voxel_f32(const SourceF32& s, float x, float y, f
     return in ? (iz * s.n[1] + iy) * s.n[0] + ix : -1;
 }
 
-__device__ __forceinline__ float bodies_f32(const SourceF32& s, float r, float x, float y, float z)
-{
-    for (int j = 0; j < s.n_prisms; ++j) {
-        const float* q = s.prisms[j];
-        const bool in = (x >= q[0]) & (x < q[3]) & (y >= q[1]) & (y < q[4]) & (z >= q[2]) & (z < q[5]);
-        r = in ? r + q[6] : r;
-    }
-    for (int j = 0; j < s.n_spheres; ++j) {
-        const float* q = s.spheres[j];
-        const float dx = x - q[0], dy = y - q[1], dz = z - q[2];
-        const bool in = dx * dx + dy * dy + dz * dz < q[3] * q[3];
-        r = in ? r + q[4] : r;
-    }
-    return r;
-}
-
-// FP32 stepping's grid lookup, branch-free like grid_in_f64 (the same voxel
+// FP32 stepping's grid lookup, branch-free like grid_fetch_f64 (the same voxel
 // as voxel_f32).
 template <bool LEVELS = false>
 __device__ __forceinline__ GridProbe grid_fetch_f32(const SourceF32& s, float x, float y, float z)
@@ -519,24 +503,6 @@ template <bool LEVELS = false>
 __device__ __forceinline__ float grid_keep_f32(const SourceF32& s, const GridProbe& p)
 {
     return probe_keep<LEVELS>(s, p);
-}
-
-template <bool LEVELS = false>
-__device__ __forceinline__ float grid_in_f32(const SourceF32& s, float x, float y, float z)
-{
-    return grid_keep_f32<LEVELS>(s, grid_fetch_f32<LEVELS>(s, x, y, z));
-}
-
-template <bool LEVELS = false>
-__device__ __forceinline__ float grid_f32(const SourceF32& s, float x, float y, float z)
-{
-    return s.has_grid ? grid_in_f32<LEVELS>(s, x, y, z) : 0.0f;
-}
-
-template <bool LEVELS = false>
-__device__ __forceinline__ float rho_f32(const SourceF32& s, float x, float y, float z)
-{
-    return bodies_f32(s, grid_f32<LEVELS>(s, x, y, z), x, y, z);
 }
 
 // ---------------------------------------------------------------------------

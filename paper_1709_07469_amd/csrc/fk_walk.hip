@@ -376,14 +376,9 @@ struct Prec<true> {
     __device__ static void normals(const Block& b, T* z, const BmTables* t) { normals_f64(b, *t, z[0], z[1]); }
     __device__ static T fmat(T a, T b, T c) { return fma(a, b, c); }
     template <bool LEVELS>
-    __device__ static T rho(const Src& s, T x, T y, T z) { return rho_f64<LEVELS>(s, x, y, z); }
-    template <bool LEVELS>
-    __device__ static T grid_in(const Src& s, T x, T y, T z) { return grid_in_f64<LEVELS>(s, x, y, z); }
-    template <bool LEVELS>
     __device__ static GridProbe grid_fetch(const Src& s, T x, T y, T z) { return grid_fetch_f64<LEVELS>(s, x, y, z); }
     template <bool LEVELS>
     __device__ static T grid_keep(const Src& s, const GridProbe& p) { return grid_keep_f64<LEVELS>(s, p); }
-    __device__ static T bodies(const Src& s, T g, T x, T y, T z) { return bodies_f64(s, g, x, y, z); }
     __device__ static int64_t voxel(const Src& s, T x, T y, T z) { return voxel_f64(s, x, y, z); }
     __device__ static T lo(const WalkCommon& C, int c) { return C.lo[c]; }
     __device__ static T hi(const WalkCommon& C, int c) { return C.hi[c]; }
@@ -414,14 +409,9 @@ struct Prec<false> {
     }
     __device__ static T fmat(T a, T b, T c) { return fmaf(a, b, c); }
     template <bool LEVELS>
-    __device__ static T rho(const Src& s, T x, T y, T z) { return rho_f32<LEVELS>(s, x, y, z); }
-    template <bool LEVELS>
-    __device__ static T grid_in(const Src& s, T x, T y, T z) { return grid_in_f32<LEVELS>(s, x, y, z); }
-    template <bool LEVELS>
     __device__ static GridProbe grid_fetch(const Src& s, T x, T y, T z) { return grid_fetch_f32<LEVELS>(s, x, y, z); }
     template <bool LEVELS>
     __device__ static T grid_keep(const Src& s, const GridProbe& p) { return grid_keep_f32<LEVELS>(s, p); }
-    __device__ static T bodies(const Src& s, T g, T x, T y, T z) { return bodies_f32(s, g, x, y, z); }
     __device__ static int64_t voxel(const Src& s, T x, T y, T z) { return voxel_f32(s, x, y, z); }
     __device__ static T lo(const WalkCommon& C, int c) { return C.lo_f[c]; }
     __device__ static T hi(const WalkCommon& C, int c) { return C.hi_f[c]; }
@@ -622,35 +612,41 @@ struct Walker {
     }
 
     // Turns the normals of the next MACRO steps into the points those steps
-    // reach (as if none ended the walk) and, with a grid, loads the grid
-    // density at each, all loads issued before the first is used.  Points past
-    // the walk's end are never used.
-    __device__ __forceinline__ void advance(const LaneProblem<F64>& P, const typename Prec<F64>::Src& src, T* z,
-                                            T* g) const
+    // reach (as if none ended the walk).  Points past the walk's end are never
+    // used.
+    __device__ __forceinline__ void advance(const LaneProblem<F64>& P, T* z) const
     {
-        constexpr int MACRO = Prec<F64>::kMacro;
         T p0 = x0, p1 = x1, p2 = x2;
 #pragma unroll
-        for (int s = 0; s < MACRO; ++s) {
+        for (int s = 0; s < Prec<F64>::kMacro; ++s) {
             p0 = Prec<F64>::fmat(P.sdt, z[3 * s], p0);
             p1 = Prec<F64>::fmat(P.sdt, z[3 * s + 1], p1);
             p2 = Prec<F64>::fmat(P.sdt, z[3 * s + 2], p2);
             z[3 * s] = p0;
             z[3 * s + 1] = p1;
             z[3 * s + 2] = p2;
-            g[s] = T(0);
         }
+    }
+
+    // The source's densities at N points: the grid's, all loads issued before
+    // the first is used, then the analytic bodies' added in their order.
+    template <int N>
+    __device__ __forceinline__ static void densities(const typename Prec<F64>::Src& src, const T* y, T* r)
+    {
+#pragma unroll
+        for (int i = 0; i < N; ++i) r[i] = T(0);
         // A launch takes the grid loop when any of its problems has a grid,
         // but a batch may mix sources with and without one: the lane's own
-        // source is checked, once for all the macro-step's loads.
-        if (!ADJ && loop_grid(LOOP) && src.has_grid) {
-            GridProbe pr[MACRO];
+        // source is checked, once for all the points' loads.
+        if (loop_grid(LOOP) && src.has_grid) {
+            GridProbe pr[N];
 #pragma unroll
-            for (int s = 0; s < MACRO; ++s)
-                pr[s] = Prec<F64>::template grid_fetch<loop_levels(LOOP)>(src, z[3 * s], z[3 * s + 1], z[3 * s + 2]);
+            for (int i = 0; i < N; ++i)
+                pr[i] = Prec<F64>::template grid_fetch<loop_levels(LOOP)>(src, y[3 * i], y[3 * i + 1], y[3 * i + 2]);
 #pragma unroll
-            for (int s = 0; s < MACRO; ++s) g[s] = Prec<F64>::template grid_keep<loop_levels(LOOP)>(src, pr[s]);
+            for (int i = 0; i < N; ++i) r[i] = Prec<F64>::template grid_keep<loop_levels(LOOP)>(src, pr[i]);
         }
+        bodies<N>(src, y, r);
     }
 
     // Adds one trapezoid term rho(a) + rho(b) to the walk's sum.
@@ -687,25 +683,24 @@ struct Walker {
     // test stopped it at face f.  The walk's point x and density rp move to
     // the macro-step's last point only when the walk goes on, so a walk that
     // ended keeps them at the macro-step's start (finish recovers the step's
-    // two ends from x and y).  g holds the grid density at each point.
+    // two ends from x and y).  rn holds the density at each point (densities;
+    // the adjoint has none).
     __device__ __forceinline__ bool steps(const LaneProblem<F64>& P, const typename Prec<F64>::Src& src, const T* y,
-                                          const T* g, int& at, int& how)
+                                          const T* rn, int& at, int& how)
     {
         constexpr int MACRO = Prec<F64>::kMacro;
         bool done = false;
         T r = rp;   // the density at the step's start
         if constexpr (!ADJ && loop_exit(LOOP) < 2) {
-            // Densities and exit tests of all the points first.  When no
+            // Exit tests of all the points first.  When no
             // walk of the wavefront ends in this macro-step -- nearly always
             // for walks of hundreds of steps -- the steps run as straight-line
             // code, without the per-step masking of walks that ended.
-            T rn[MACRO];
             bool out[MACRO];
             bool end = (int64_t)n + MACRO >= P.max_steps;
 #pragma unroll
             for (int s = 0; s < MACRO; ++s) {
                 T d2;
-                rn[s] = Prec<F64>::bodies(src, g[s], y[3 * s], y[3 * s + 1], y[3 * s + 2]);
                 out[s] = leaves(P, y[3 * s], y[3 * s + 1], y[3 * s + 2], d2);
                 end = end | out[s];
             }
@@ -739,10 +734,9 @@ struct Walker {
             for (int s = 0; s < MACRO; ++s) {
                 if (done) break;
                 const T y0 = y[3 * s], y1 = y[3 * s + 1], y2 = y[3 * s + 2];
-                T rn = T(0);
                 if (!ADJ) {
-                    rn = Prec<F64>::bodies(src, g[s], y0, y1, y2);
-                    add_trapezoid(r, rn);
+                    add_trapezoid(r, rn[s]);
+                    r = rn[s];
                 }
                 n += 1;
                 T d2;
@@ -766,7 +760,6 @@ struct Walker {
                     at = s;
                     done = true;
                 }
-                r = rn;
             }
         }
         if (!done) {
@@ -939,7 +932,7 @@ __device__ __forceinline__ void coop_round(Walker<F64, KAHAN, false, LOOP>& W, c
     wave_sync_lds();
 
     // 2. densities and exit tests: point t = s m + w in lane t mod 64
-    T y[3 * MACRO], g[MACRO];
+    T y[3 * MACRO], rn[MACRO];
 #pragma unroll
     for (int i = 0; i < MACRO; ++i) {
         int t = lane + 64 * i;
@@ -947,16 +940,8 @@ __device__ __forceinline__ void coop_round(Walker<F64, KAHAN, false, LOOP>& W, c
         const int s = (t * over) >> 16, w = t - s * m;
 #pragma unroll
         for (int c = 0; c < 3; ++c) y[3 * i + c] = zb[at(s, c, w)];
-        g[i] = T(0);
     }
-    if (loop_grid(LOOP) && src.has_grid) {
-        GridProbe pr[MACRO];
-#pragma unroll
-        for (int i = 0; i < MACRO; ++i)
-            pr[i] = Prec<F64>::template grid_fetch<loop_levels(LOOP)>(src, y[3 * i], y[3 * i + 1], y[3 * i + 2]);
-#pragma unroll
-        for (int i = 0; i < MACRO; ++i) g[i] = Prec<F64>::template grid_keep<loop_levels(LOOP)>(src, pr[i]);
-    }
+    Walker<F64, KAHAN, false, LOOP>::template densities<MACRO>(src, y, rn);
     bool some = false, mass = false;
     uint32_t ends = 0;                            // bit i: point i ends its walk
     int hows[MACRO];
@@ -968,9 +953,8 @@ __device__ __forceinline__ void coop_round(Walker<F64, KAHAN, false, LOOP>& W, c
         const int from = lanes[w];
         const uint32_t nw = (uint32_t)__shfl((int)W.n, from);
         const T y0 = y[3 * i], y1 = y[3 * i + 1], y2 = y[3 * i + 2];
-        const T rn = Prec<F64>::bodies(src, g[i], y0, y1, y2);
-        if (valid) R.dens[t] = rn;
-        mass = mass | (valid & !(rn == T(0)));
+        if (valid) R.dens[t] = rn[i];
+        mass = mass | (valid & !(rn[i] == T(0)));
         T d2;
         const bool out = Walker<F64, KAHAN, false, LOOP>::leaves(P, y0, y1, y2, d2);
         int stop = -1;
@@ -1236,11 +1220,8 @@ __device__ __forceinline__ void walk_body(const Args& A)
                     W.sc.sign = ti.w ? -1 : 1;
                     W.sc.add(Prec<F64>::voxel(source(), W.x0, W.x1, W.x2), 1);
                 } else {
-                    // a launch without the grid loop has no grid in any source
-                    if constexpr (loop_grid(LOOP))
-                        W.rp = Prec<F64>::template rho<loop_levels(LOOP)>(source(), W.x0, W.x1, W.x2);
-                    else
-                        W.rp = Prec<F64>::bodies(source(), T(0), W.x0, W.x1, W.x2);
+                    const T start[3] = {W.x0, W.x1, W.x2};
+                    Walker<F64, KAHAN, ADJ, LOOP, DENSE>::template densities<1>(source(), start, &W.rp);
                 }
                 W.deep = false;
                 if (loop_exit(LOOP) == 2 && P.bridge) {
@@ -1276,12 +1257,13 @@ __device__ __forceinline__ void walk_body(const Args& A)
                 Prec<F64>::normals(bl, z + NPB * b, bmt);
             }
             W.k += 3;
+            W.advance(P, z);
             bool done = false;
             int how = 0, at = 0;
             with_source([&](const typename Prec<F64>::Src& src) {
-                T g[MACRO];
-                W.advance(P, src, z, g);
-                done = W.steps(P, src, z, g, at, how);
+                T r[MACRO];
+                if constexpr (!ADJ) W.template densities<MACRO>(src, z, r);
+                done = W.steps(P, src, z, r, at, how);
             });
             if (done) W.finish(P, z, at, how);
         }
@@ -1369,10 +1351,11 @@ __device__ __forceinline__ void walk_body(const Args& A)
                         zz[c] = tail_z[wave][(q / NPB) * m + rank][q % NPB];
                     }
                     int at = 0;
+                    W.advance(P, zz);
                     with_source([&](const typename Prec<F64>::Src& src) {
-                        T g[MACRO];
-                        W.advance(P, src, zz, g);
-                        done = W.steps(P, src, zz, g, at, how);
+                        T r[MACRO];
+                        if constexpr (!ADJ) W.template densities<MACRO>(src, zz, r);
+                        done = W.steps(P, src, zz, r, at, how);
                     });
                     if (done) W.finish(P, zz, at, how);
                 }

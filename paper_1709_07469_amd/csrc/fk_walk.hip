@@ -341,15 +341,16 @@ struct Scatter {
     }
 };
 
-// The launch's one generator key, in scalar registers and opaque from here on:
-// the ten rounds' keys are then scalar additions of every macro-step (the
-// scalar unit is idle) instead of twenty values kept over the whole loop.
-// FP64 walks, whose constants fill the scalar registers, got those back from
-// spill lanes, 18 VALU lane reads a macro-step; mixed walks hold them without
-// spilling and are 1.5 % faster so (the 32-model batch).
-__device__ __forceinline__ void scalar_key(uint32_t& key0, uint32_t& key1)
+// The launch's one generator key, in scalar registers and, by the empty asm's
+// dependence on the round's number, a new value in every round: the ten
+// rounds' keys are then scalar additions of every macro-step (the scalar unit
+// is idle) instead of twenty values kept over the whole loop, which overflow
+// the scalar registers and come back through VALU lane reads, 16 to 20 a
+// macro-step.  Mixed batches hold the twenty without spilling and are 1.5 %
+// faster so (the 32-model batch).
+__device__ __forceinline__ void scalar_key(uint32_t& key0, uint32_t& key1, uint64_t round)
 {
-    asm volatile("" : "+s"(key0), "+s"(key1));
+    asm("" : "+s"(key0), "+s"(key1) : "s"((uint32_t)round));
 }
 
 // ---------------------------------------------------------------------------
@@ -483,7 +484,7 @@ struct LaneProblem {
     T dt, delta;               // Brownian-bridge test
     bool ball, bridge;
     uint32_t key0, key1, pid;
-    int64_t max_steps;
+    uint32_t max_steps;        // at most 2^31 - 1
 
     // keys = false leaves key0 and key1 as they are (a batch whose problems
     // share the generator key holds it in scalar registers, set once).
@@ -515,7 +516,7 @@ struct LaneProblem {
             key1 = c.key1;
         }
         pid = c.problem_id;
-        max_steps = c.max_steps;
+        max_steps = (uint32_t)c.max_steps;
     }
 
     // Takes lane l's problem (the same in every lane afterwards).
@@ -539,7 +540,7 @@ struct LaneProblem {
             key1 = (uint32_t)__builtin_amdgcn_readlane((int)o.key1, l);
         }
         pid = (uint32_t)__builtin_amdgcn_readlane((int)o.pid, l);
-        max_steps = (int64_t)lane_u64((uint64_t)o.max_steps, l);
+        max_steps = (uint32_t)__builtin_amdgcn_readlane((int)o.max_steps, l);
     }
 };
 
@@ -562,9 +563,9 @@ struct Walker {
     uint64_t rec;    // the walk's record slot (its task minus the launch's first task)
     ExitRecord* exits;
     uint32_t* steps_out;
-    T x0, x1, x2, rp;
-    double S;        // trapezoid sum (FP64 accumulation)
-    float Sf, Sc;    // Kahan sum and compensation
+    T x0, x1, x2;
+    double S;        // sum of densities (add_density), FP64 accumulation
+    float Sf, Sc;    // or Kahan sum and compensation
     uint32_t n, k, sctr, pctr;
     bool active;
     bool deep;       // the current point lies delta inside every face (bridge test)
@@ -649,19 +650,29 @@ struct Walker {
         bodies<N>(src, y, r);
     }
 
-    // Adds one trapezoid term rho(a) + rho(b) to the walk's sum.
-    __device__ __forceinline__ void add_trapezoid(T a, T b)
+    // Adds a point's density r to the walk's sum of densities, in which the
+    // walk's first and last point count half: half the trapezoid sum
+    // sum_n (rho_n + rho_{n+1}), in one addition a step (two, and the density
+    // of the step before in registers, when every step added its two ends).
+    // Kahan g_z of the SI prism 93.5 -> 88.8 ms, the paper's bridge g_z, mixed,
+    // 2.61 -> 2.43 ms (with the round keys of scalar_key).
+    __device__ __forceinline__ void add_density(T r)
     {
-        if (F64) {
-            S = S + (double)(a + b);
-        } else if (KAHAN) {
-            const float t0 = (float)(a + b) - Sc;
+        if (KAHAN && !F64) {
+            const float t0 = (float)r - Sc;
             const float t = Sf + t0;
             Sc = (t - Sf) - t0;
             Sf = t;
         } else {
-            S = S + ((double)a + (double)b);
+            S = S + (double)r;
         }
+    }
+
+    __device__ __forceinline__ void start_sum(T r)
+    {
+        S = KAHAN && !F64 ? 0.0 : 0.5 * (double)r;
+        Sf = KAHAN && !F64 ? 0.5f * (float)r : 0.0f;
+        Sc = 0.0f;
     }
 
     // Whether y has left the domain (on the boundary counts as left); d2 is
@@ -680,24 +691,23 @@ struct Walker {
     // each with its density and exit test, up to the first that ends the
     // walk.  Returns true when the walk ended, at step at, with how = 0: it
     // left the domain; how = 1: it reached max_steps; how = 2 + f: the bridge
-    // test stopped it at face f.  The walk's point x and density rp move to
-    // the macro-step's last point only when the walk goes on, so a walk that
-    // ended keeps them at the macro-step's start (finish recovers the step's
-    // two ends from x and y).  rn holds the density at each point (densities;
-    // the adjoint has none).
+    // test stopped it at face f.  The walk's point x moves to the macro-step's
+    // last point only when the walk goes on, so a walk that ended keeps it at
+    // the macro-step's start (finish recovers the last step's two ends from x
+    // and y).  rn holds the density at each point (densities; the
+    // adjoint has none).
     __device__ __forceinline__ bool steps(const LaneProblem<F64>& P, const typename Prec<F64>::Src& src, const T* y,
                                           const T* rn, int& at, int& how)
     {
         constexpr int MACRO = Prec<F64>::kMacro;
         bool done = false;
-        T r = rp;   // the density at the step's start
         if constexpr (!ADJ && loop_exit(LOOP) < 2) {
-            // Exit tests of all the points first.  When no
-            // walk of the wavefront ends in this macro-step -- nearly always
-            // for walks of hundreds of steps -- the steps run as straight-line
-            // code, without the per-step masking of walks that ended.
+            // Exit tests of all the points first.  When no walk of the
+            // wavefront ends in this macro-step -- nearly always for walks of
+            // hundreds of steps -- the steps run as straight-line code,
+            // without the per-step masking of walks that ended.
             bool out[MACRO];
-            bool end = (int64_t)n + MACRO >= P.max_steps;
+            bool end = n + MACRO >= P.max_steps;
 #pragma unroll
             for (int s = 0; s < MACRO; ++s) {
                 T d2;
@@ -706,27 +716,25 @@ struct Walker {
             }
             if (__ballot(end) == 0ull) {
 #pragma unroll
-                for (int s = 0; s < MACRO; ++s) {
-                    add_trapezoid(r, rn[s]);
-                    r = rn[s];
-                }
+                for (int s = 0; s < MACRO; ++s) add_density(rn[s]);
                 n += MACRO;
             } else {
 #pragma unroll
                 for (int s = 0; s < MACRO; ++s) {
                     if (done) break;
-                    add_trapezoid(r, rn[s]);
                     n += 1;
+                    T r = rn[s];
                     if (out[s]) {
                         how = 0;
                         at = s;
                         done = true;
-                    } else if ((int64_t)n == P.max_steps) {
+                        r = T(0.5) * r;
+                    } else if (n == P.max_steps) {
                         how = 1;
                         at = s;
                         done = true;
                     }
-                    r = rn[s];
+                    add_density(r);
                 }
             }
         } else {
@@ -734,10 +742,6 @@ struct Walker {
             for (int s = 0; s < MACRO; ++s) {
                 if (done) break;
                 const T y0 = y[3 * s], y1 = y[3 * s + 1], y2 = y[3 * s + 2];
-                if (!ADJ) {
-                    add_trapezoid(r, rn[s]);
-                    r = rn[s];
-                }
                 n += 1;
                 T d2;
                 const bool out = leaves(P, y0, y1, y2, d2);
@@ -755,18 +759,18 @@ struct Walker {
                     how = out ? 0 : 2 + stop;
                     at = s;
                     done = true;
-                } else if ((int64_t)n == P.max_steps) {
+                } else if (n == P.max_steps) {
                     how = 1;
                     at = s;
                     done = true;
                 }
+                if (!ADJ) add_density(done ? T(0.5) * rn[s] : rn[s]);
             }
         }
         if (!done) {
             x0 = y[3 * MACRO - 3];
             x1 = y[3 * MACRO - 2];
             x2 = y[3 * MACRO - 1];
-            rp = r;
         }
         return done;
     }
@@ -828,7 +832,7 @@ struct Walker {
                         intersect_exit(C.lo, C.hi, a, b, e);
                 }
             }
-            const double sum = (!F64 && KAHAN) ? ((double)Sf - (double)Sc) : S;
+            const double sum = 2.0 * ((!F64 && KAHAN) ? ((double)Sf - (double)Sc) : S);
             exits[rec] = ExitRecord{e[0], e[1], e[2], sum};
             steps_out[rec] = n | (capped ? kCapFlag : 0u);
         }
@@ -846,7 +850,7 @@ struct Walker {
 //      replacing its normals in LDS by the positions they lead to;
 //   2. all 64 lanes take densities and exit tests of the round's points, up
 //      to MACRO points each, all grid loads in flight together;
-//   3. the lane that holds a walk adds its trapezoid terms in step order, up
+//   3. the lane that holds a walk adds its densities in step order, up
 //      to the first point that ends it (nothing to add when every density of
 //      the round is zero).
 // The arithmetic of every step and its order are those of a macro-step, so a
@@ -972,7 +976,7 @@ __device__ __forceinline__ void coop_round(Walker<F64, KAHAN, false, LOOP>& W, c
                     stop = W.bridge_stop(P, pw, sw, nw + (uint32_t)s, a0, a1, a2, y0, y1, y2);
             }
         }
-        const bool end = valid & (out | (stop >= 0) | ((int64_t)nw + s + 1 >= P.max_steps));
+        const bool end = valid & (out | (stop >= 0) | (nw + (uint32_t)s + 1u >= P.max_steps));
         hows[i] = out ? 0 : stop >= 0 ? 2 + stop : 1;
         if (end) {
             atomicMin(&R.end[w], s);
@@ -980,7 +984,7 @@ __device__ __forceinline__ void coop_round(Walker<F64, KAHAN, false, LOOP>& W, c
         }
         some = some | end;
     }
-    const bool any_mass = __ballot(mass | (W.active & !(W.rp == T(0)))) != 0ull;
+    const bool any_mass = __ballot(mass) != 0ull;
     const bool any_end = __ballot(some) != 0ull;
     wave_sync_lds();
     if (any_end) {
@@ -1001,19 +1005,14 @@ __device__ __forceinline__ void coop_round(Walker<F64, KAHAN, false, LOOP>& W, c
         const int taken = f < L ? f + 1 : L;
         // a sum of zeros leaves an uncompensated sum as it is
         if (KAHAN || any_mass) {
-            T r = W.rp;
             for (int s = 0; s < taken; s += 8) {
                 T d[8];
 #pragma unroll
                 for (int i = 0; i < 8; ++i) d[i] = R.dens[(s + i < L ? s + i : L - 1) * m + rank];
 #pragma unroll
                 for (int i = 0; i < 8; ++i)
-                    if (s + i < taken) {
-                        W.add_trapezoid(r, d[i]);
-                        r = d[i];
-                    }
+                    if (s + i < taken) W.add_density(s + i == f ? T(0.5) * d[i] : d[i]);
             }
-            W.rp = r;
         }
         W.n += (uint32_t)taken;
         W.k += (uint32_t)(3 * macros);
@@ -1084,7 +1083,7 @@ __device__ __forceinline__ void walk_body(const Args& A)
             P.key0 = A.key0;
             P.key1 = A.key1;
         }
-        P.max_steps = 0;
+        P.max_steps = 0u;
     } else {
         Q = Queue{A.c.queue, (uint64_t)A.c.n_tasks, (uint32_t)A.c.grab, A.c.total_waves, A.c.stripes,
                   A.c.refill_cost, A.c.cap};
@@ -1140,7 +1139,7 @@ __device__ __forceinline__ void walk_body(const Args& A)
         W.exits = A.c.exits;
         W.steps_out = A.c.steps;
     }
-    W.x0 = W.x1 = W.x2 = W.rp = T(0);
+    W.x0 = W.x1 = W.x2 = T(0);
     W.S = 0.0;
     W.Sf = W.Sc = 0.0f;
     W.n = W.k = W.sctr = W.pctr = 0;
@@ -1221,7 +1220,9 @@ __device__ __forceinline__ void walk_body(const Args& A)
                     W.sc.add(Prec<F64>::voxel(source(), W.x0, W.x1, W.x2), 1);
                 } else {
                     const T start[3] = {W.x0, W.x1, W.x2};
-                    Walker<F64, KAHAN, ADJ, LOOP, DENSE>::template densities<1>(source(), start, &W.rp);
+                    T r;
+                    Walker<F64, KAHAN, ADJ, LOOP, DENSE>::template densities<1>(source(), start, &r);
+                    W.start_sum(r);
                 }
                 W.deep = false;
                 if (loop_exit(LOOP) == 2 && P.bridge) {
@@ -1250,7 +1251,7 @@ __device__ __forceinline__ void walk_body(const Args& A)
             // ---- macro-step: 3 blocks of this lane's own walk ----
             T z[3 * NPB];
             uint32_t key0 = P.key0, key1 = P.key1;
-            if constexpr (F64 && (!BATCH || UKEY)) scalar_key(key0, key1);
+            if constexpr (!BATCH || (F64 && UKEY)) scalar_key(key0, key1, pool.rounds);
 #pragma unroll
             for (int b = 0; b < 3; ++b) {
                 const Block bl = philox10(W.k + b, W.pctr, W.sctr, P.pid, key0, key1);
@@ -1297,7 +1298,7 @@ __device__ __forceinline__ void walk_body(const Args& A)
                 const uint32_t ps = (uint32_t)__shfl((int)W.pctr, src);
                 const uint32_t ss = (uint32_t)__shfl((int)W.sctr, src);
                 uint32_t key0 = P.key0, key1 = P.key1, pid = P.pid;
-                if constexpr (F64 && (!BATCH || UKEY)) scalar_key(key0, key1);
+                if constexpr (!BATCH || (F64 && UKEY)) scalar_key(key0, key1, pool.rounds);
                 if constexpr (BATCH) {
                     if constexpr (!UKEY) {
                         key0 = (uint32_t)__shfl((int)P.key0, src);

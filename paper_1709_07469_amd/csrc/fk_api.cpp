@@ -8,8 +8,10 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <limits>
 #include <mutex>
 #include <string>
+#include <type_traits>
 #include <utility>
 #include <vector>
 
@@ -470,24 +472,129 @@ void fill_source_f32(fk::SourceF32& S, const fk_source* s)
         for (int c = 0; c < 5; ++c) S.spheres[j][c] = (float)s->spheres[5 * j + c];
 }
 
+// The first x in (lo, hi] with index(x) >= k, in T's own numbers, for an index
+// that does not decrease with x; hi's successor if there is none.  Searched
+// over the numbers in their order, from a guess that is mostly a few numbers
+// off (a handful of evaluations: a batch does six searches a problem).
+template <class T, class F>
+T first_at(T lo, T hi, double k, double guess, F&& index)
+{
+    using I = typename std::conditional<sizeof(T) == 8, int64_t, int32_t>::type;
+    auto rank = [](T x) {       // signed magnitude to two's complement, so that ranks order like numbers
+        I b;
+        std::memcpy(&b, &x, sizeof b);
+        return b < 0 ? (I)(std::numeric_limits<I>::min() - b) : b;
+    };
+    auto number = [](I r) {
+        const I b = r < 0 ? (I)(std::numeric_limits<I>::min() - r) : r;
+        T x;
+        std::memcpy(&x, &b, sizeof x);
+        return x;
+    };
+    I a = rank(lo), b = rank(hi) + 1;                       // index < k up to a, >= k from b on
+    I at = rank((T)std::min(std::max(guess, (double)lo), (double)hi));
+    for (I step = 1; a < at && at < b && step < (I)1 << 20; step *= 2) {
+        if (index(number(at)) >= k) b = at, at -= step;
+        else a = at, at += step;
+        if (a + 1 >= b) break;
+    }
+    while (a + 1 < b) {
+        const I m = (a >> 1) + (b >> 1) + (a & b & 1);      // between a and b, without overflow
+        if (index(number(m)) >= k) b = m;
+        else a = m;
+    }
+    return number(b);
+}
+
+// The bounds between which a point lies strictly inside [lo, hi] and its index
+// in [0, n): x > in_lo and x < in_hi.
+template <class T, class F>
+void inner_axis(T lo, T hi, double origin, double spacing, int32_t n, F&& index, T* in_lo, T* in_hi)
+{
+    *in_lo = std::max(lo, std::nextafter(first_at(lo, hi, 0.0, origin, index), -std::numeric_limits<T>::infinity()));
+    *in_hi = std::min(hi, first_at(lo, hi, (double)n, origin + n * spacing, index));
+}
+
+// All but 1/256 of the box between the inner bounds: nearly every macro-step of
+// a walk is then a plain one.
+bool nearly_all(double lo, double hi, double in_lo, double in_hi)
+{
+    return in_hi - in_lo >= (1.0 - 1.0 / 256) * (hi - lo);
+}
+
+// Whether a solve takes the covering loop -- its grid covers the box, its
+// exit test is the box's, and the grid's addresses fit the buffer lookup
+// (layers below 2^24 voxels, the grid below 2^32 bytes) -- and the source's
+// inner bounds.  With `shared` the source serves several problems and keeps
+// the bounds that hold for all of them.
+// The FP64 lookup's margin bounds what rounding can do to a coordinate
+// x / spacing - origin / spacing: half an ulp in 1/spacing, in origin/spacing
+// and in the fma, and one each in the subtraction and the division that
+// define the voxel, together below 2^-51 times the sum of the magnitudes; a
+// grid so far from the origin that this exceeds 2^-12 of a voxel takes the
+// general loop.
+bool cover_shape(const fk_params* p, const fk_source* s)
+{
+    return has_grid(s) && p->domain == FK_DOMAIN_BOX && p->exit_rule != FK_EXIT_BRIDGE &&
+           (int64_t)s->n[0] * s->n[1] < (1ll << 24) && (int64_t)s->n[0] * s->n[1] * s->n[2] < (1ll << 30);
+}
+
+bool covers(fk::SourceF64& S, const fk_params* p, const fk_box* box, const fk_source* s, bool shared = false)
+{
+    if (!cover_shape(p, s)) return false;
+    bool all = true;
+    double margin = 0.0;
+    for (int c = 0; c < 3; ++c) {
+        const double o = s->origin[c], d = s->spacing[c];
+        double lo, hi;
+        inner_axis(box->lo[c], box->hi[c], o, d, s->n[c], [&](double x) { return std::floor((x - o) / d); }, &lo, &hi);
+        S.in_lo[c] = shared ? std::max(S.in_lo[c], lo) : lo;
+        S.in_hi[c] = shared ? std::min(S.in_hi[c], hi) : hi;
+        S.obh[c] = (double)(-(long double)o / d - 0.5L);
+        all = all && nearly_all(box->lo[c], box->hi[c], S.in_lo[c], S.in_hi[c]);
+        // a point reaches at most 8.6 sqrt(dt) beyond the box
+        const double x = std::max(std::fabs(box->lo[c]), std::fabs(box->hi[c])) + 9.0 * std::sqrt(p->dt);
+        margin = std::max(margin, 0x1p-51 * ((x + std::fabs(o)) / d + s->n[c] + 2.0));
+    }
+    S.near = std::min(shared ? S.near : 0.5, 0.5 - margin);
+    return all && margin <= 0x1p-12;
+}
+
+bool covers(fk::SourceF32& S, const fk_params* p, const fk_box* box, const fk_source* s, bool shared = false)
+{
+    if (!cover_shape(p, s)) return false;
+    bool all = true;
+    for (int c = 0; c < 3; ++c) {
+        const float blo = (float)box->lo[c], bhi = (float)box->hi[c], inv = S.inv[c], ob = S.ob[c];
+        float lo, hi;
+        inner_axis(blo, bhi, s->origin[c], s->spacing[c], s->n[c],
+                   [&](float x) { return std::floor(std::fma(x, inv, ob)); }, &lo, &hi);
+        S.in_lo[c] = shared ? std::max(S.in_lo[c], lo) : lo;
+        S.in_hi[c] = shared ? std::min(S.in_hi[c], hi) : hi;
+        all = all && nearly_all(blo, bhi, S.in_lo[c], S.in_hi[c]);
+    }
+    return all;
+}
+
 // The stepping loop a problem needs: 0 box, 1 ball exit test, 2 bridge test;
 // plus 4 when its source has a voxel grid (the loop then loads grid values
-// ahead), and 8 more when that grid is given by levels.  A batch takes the
-// most general exit test and the grid bits of any (its grids must all be of
-// one kind, which check_batch ensures).
-int loop_kind(const fk_params* p, const fk_source* s)
+// ahead), 8 more when that grid is given by levels and 16 more when it covers
+// the box.  A batch takes the most general exit test and the grid bits of any
+// (its grids must all be of one kind, which check_batch ensures), and the
+// covering loop when every problem's grid covers its box.
+int loop_kind(const fk_params* p, const fk_source* s, bool cover = false)
 {
     const int e = p->exit_rule == FK_EXIT_BRIDGE ? 2 : p->domain == FK_DOMAIN_BALL ? 1 : 0;
-    return e | (has_grid(s) ? 4 : 0) | (s && s->rho_index ? 8 : 0);
+    return e | (has_grid(s) ? 4 : 0) | (s && s->rho_index ? 8 : 0) | (cover ? 16 : 0);
 }
 
 int merge_loops(int a, int b)
 {
-    return std::max(a & 3, b & 3) | ((a | b) & 12);
+    return std::max(a & 3, b & 3) | ((a | b) & 12) | (a & b & 16);
 }
 
-fk_status plan_launch(int precision, int64_t n_tasks, fk::LaunchCfg* cfg, bool batch = false, int loop = 0,
-                      bool shared = false, bool adjoint = false, bool ukey = false)
+fk_status plan_loop(int precision, int64_t n_tasks, fk::LaunchCfg* cfg, bool batch, int loop, bool shared,
+                    bool adjoint, bool ukey)
 {
     fk_launch l;
     {
@@ -525,6 +632,20 @@ fk_status plan_launch(int precision, int64_t n_tasks, fk::LaunchCfg* cfg, bool b
     cfg->stripes = l.stripes > 0 ? (uint32_t)l.stripes : (batch && !shared ? 8u : 1u);
     cfg->refill_cost = l.refill_cost > 0 ? (uint32_t)l.refill_cost : 64u;
     return FK_OK;
+}
+
+// The launch and its loop.  Launches of few walks run in drain rounds from
+// their start, which the covering lookup has no part in: they take the general
+// loop, whose kernels need fewer registers there.
+fk_status plan_launch(int precision, int64_t n_tasks, fk::LaunchCfg* cfg, int* loop, bool batch = false,
+                      bool shared = false, bool adjoint = false, bool ukey = false)
+{
+    fk_status st = plan_loop(precision, n_tasks, cfg, batch, *loop, shared, adjoint, ukey);
+    if (st == FK_OK && cfg->cap < 64u && (*loop & 16)) {
+        *loop &= ~16;
+        st = plan_loop(precision, n_tasks, cfg, batch, *loop, shared, adjoint, ukey);
+    }
+    return st;
 }
 
 // Checks every argument of a single solve except the workspace.
@@ -580,7 +701,8 @@ fk_status run_solve(int32_t kind, const double* stations, int64_t n_stations, co
     }
     fill_bc(R.bc, bc);
 
-    const int loop = loop_kind(p, src);
+    const int loop = loop_kind(p, src, p->precision == FK_F64 ? covers(A64.src, p, box, src)
+                                                              : covers(A32.src, p, box, src));
     bool first = true;
     const std::vector<Shape> shapes{Shape{n_stations, p->paths_per_station, C.npair, L.n_chunks}};
     fk_status st = for_each_slice(shapes, L.held, [&](const Slice& sl) -> fk_status {
@@ -589,7 +711,8 @@ fk_status run_solve(int32_t kind, const double* stations, int64_t n_stations, co
         first = false;
         if (e != hipSuccess) return fail(FK_EDEVICE, "queue reset launch failed: %s", hipGetErrorString(e));
         fk::LaunchCfg cfg;
-        fk_status ps = plan_launch(p->precision, sl.t1 - sl.t0, &cfg, false, loop);
+        int slice_loop = loop;
+        fk_status ps = plan_launch(p->precision, sl.t1 - sl.t0, &cfg, &slice_loop);
         if (ps != FK_OK) return ps;
         C.task0 = sl.t0;
         C.n_tasks = sl.t1 - sl.t0;
@@ -602,10 +725,10 @@ fk_status run_solve(int32_t kind, const double* stations, int64_t n_stations, co
         const bool timed = timing && timing_begin(&ev, stream);
         if (p->precision == FK_F64) {
             A64.c = C;
-            e = fk::launch_walk_f64(A64, cfg, stream);
+            e = fk::launch_walk_f64(A64, cfg, stream, slice_loop);
         } else {
             A32.c = C;
-            e = fk::launch_walk_f32(A32, p->precision == FK_MIXED_KAHAN, cfg, stream);
+            e = fk::launch_walk_f32(A32, p->precision == FK_MIXED_KAHAN, cfg, stream, slice_loop);
         }
         if (timed) timing_end(ev, stream);
         if (e != hipSuccess) return fail(FK_EDEVICE, "walk launch failed: %s", hipGetErrorString(e));
@@ -735,12 +858,9 @@ fk_status solve_batch(const fk_problem* probs, int32_t n, fk_stat* out, void* wo
     char* ws = static_cast<char*>(workspace);
     const int precision = probs[0].params.precision;
 
-    int loop = 0;
+    int loop = 16;
     bool strict = false;
-    for (int32_t m = 0; m < n; ++m) {
-        loop = merge_loops(loop, loop_kind(&probs[m].params, &probs[m].source));
-        strict = strict || probs[m].params.strict;
-    }
+    for (int32_t m = 0; m < n; ++m) strict = strict || probs[m].params.strict;
     // one source for the whole batch (e.g. u and g_z of one model): the walk
     // kernel then reads it from its arguments instead of per-lane descriptors
     fk::BatchArgs A;
@@ -782,8 +902,15 @@ fk_status solve_batch(const fk_problem* probs, int32_t n, fk_stat* out, void* wo
         fk::BatchDesc D;
         std::memset(&D, 0, sizeof D);
         fill_common(D.c, P.kind, P.stations, P.n_stations, &P.box, &P.params, L, nullptr);
-        if (precision == FK_F64) fill_source_f64(D.s64, &P.source);
-        else fill_source_f32(D.s32, &P.source);
+        bool cover;
+        if (precision == FK_F64) {
+            fill_source_f64(D.s64, &P.source);
+            cover = covers(shared ? A.src64 : D.s64, &P.params, &P.box, &P.source, shared && m > 0);
+        } else {
+            fill_source_f32(D.s32, &P.source);
+            cover = covers(shared ? A.src32 : D.s32, &P.params, &P.box, &P.source, shared && m > 0);
+        }
+        loop = merge_loops(loop, loop_kind(&P.params, &P.source, cover));
         fill_bc(D.bc, &P.bc);
         D.out = out + P.out_offset;
         D.n_chunks = L.n_chunks;
@@ -795,6 +922,13 @@ fk_status solve_batch(const fk_problem* probs, int32_t n, fk_stat* out, void* wo
                                    (int64_t)(sizeof D / 8), stream);
         if (e != hipSuccess) return fail(FK_EDEVICE, "descriptor upload failed: %s", hipGetErrorString(e));
     }
+    if (shared)     // the common bounds must leave every problem nearly all of its box
+        for (int32_t m = 0; m < n && (loop & 16); ++m)
+            for (int c = 0; c < 3; ++c)
+                if (!(precision == FK_F64
+                          ? nearly_all(probs[m].box.lo[c], probs[m].box.hi[c], A.src64.in_lo[c], A.src64.in_hi[c])
+                          : nearly_all(probs[m].box.lo[c], probs[m].box.hi[c], A.src32.in_lo[c], A.src32.in_hi[c])))
+                    loop &= ~16;
     e = fk::launch_write_words(reinterpret_cast<uint64_t*>(ws + BL.task_off),
                                reinterpret_cast<const uint64_t*>(BL.tasks.data()), n + 1, stream);
     if (e == hipSuccess)
@@ -822,7 +956,9 @@ fk_status solve_batch(const fk_problem* probs, int32_t n, fk_stat* out, void* wo
         first = false;
         if (le != hipSuccess) return fail(FK_EDEVICE, "queue reset launch failed: %s", hipGetErrorString(le));
         fk::LaunchCfg cfg;
-        fk_status ps = plan_launch(precision, sl.t1 - sl.t0, &cfg, true, loop, shared, false, A.uniform_key != 0);
+        int slice_loop = loop;
+        fk_status ps = plan_launch(precision, sl.t1 - sl.t0, &cfg, &slice_loop, true, shared, false,
+                                   A.uniform_key != 0);
         if (ps != FK_OK) return ps;
         A.task0 = sl.t0;
         A.n_tasks = sl.t1 - sl.t0;
@@ -834,7 +970,7 @@ fk_status solve_batch(const fk_problem* probs, int32_t n, fk_stat* out, void* wo
         A.cap = cfg.cap;
         std::pair<hipEvent_t, hipEvent_t> ev{nullptr, nullptr};
         const bool timed = timing_begin(&ev, stream);
-        le = fk::launch_batch_walk(A, cfg, stream, loop, shared);
+        le = fk::launch_batch_walk(A, cfg, stream, slice_loop, shared);
         if (timed) timing_end(ev, stream);
         if (le != hipSuccess) return fail(FK_EDEVICE, "batch walk launch failed: %s", hipGetErrorString(le));
         le = fk::launch_batch_chunks(A, sl.q1 - sl.q0, stream);
@@ -930,7 +1066,8 @@ fk_status adjoint(int32_t kind, const double* stations, int64_t n_stations, cons
         cfg.stripes = 1;
         cfg.refill_cost = l.refill_cost > 0 ? (uint32_t)l.refill_cost : 64u;
         cfg.cap = 64;
-    } else if ((st = plan_launch(p->precision, L.n_tasks, &cfg, false, loop_kind(p, nullptr), false, true)) != FK_OK) {
+    } else if ((st = plan_loop(p->precision, L.n_tasks, &cfg, false, loop_kind(p, nullptr), false, true, false)) !=
+               FK_OK) {
         return st;
     }
     fk::WalkCommon C;
@@ -958,12 +1095,12 @@ fk_status adjoint(int32_t kind, const double* stations, int64_t n_stations, cons
         fk::WalkArgsF64 A;
         A.c = C;
         fill_source_f64(A.src, src);
-        e = fk::launch_walk_f64(A, cfg, stream, true, dense);
+        e = fk::launch_walk_f64(A, cfg, stream, loop_kind(p, nullptr), true, dense);
     } else {
         fk::WalkArgsF32 A;
         A.c = C;
         fill_source_f32(A.src, src);
-        e = fk::launch_walk_f32(A, p->precision == FK_MIXED_KAHAN, cfg, stream, true, dense);
+        e = fk::launch_walk_f32(A, p->precision == FK_MIXED_KAHAN, cfg, stream, loop_kind(p, nullptr), true, dense);
     }
     if (timed) timing_end(ev, stream);
     if (e != hipSuccess) return fail(FK_EDEVICE, "adjoint walk launch failed: %s", hipGetErrorString(e));

@@ -457,6 +457,30 @@ __device__ __forceinline__ double grid_keep_f64(const SourceF64& s, const GridPr
     return (double)probe_keep<LEVELS>(s, p);
 }
 
+// Covering loops (fk_walk.hip) look a voxel up before they know that the
+// point lies in the grid: the index is not clamped, and the value is loaded
+// through a buffer descriptor of the grid, whose range check returns 0 for an
+// address outside it.  covered_index gives the indices, exact for a point in
+// the grid:
+//   FP64: with q = x / spacing - origin / spacing - 1/2 from one fma and t the
+//   nearest integer, the index is t unless |q - t| comes within the rounding
+//   margin of 1/2 (SourceF64::near; worst collects the largest): five
+//   operations an axis instead of the eleven of grid_axis_f64 and its clamp;
+//   FP32: axis_f32, the definition itself.
+__device__ __forceinline__ int near_axis_f64(double x, double inv, double obh, double& worst)
+{
+    const double q = fma(x, inv, obh);
+    const double t = __builtin_rint(q);
+    worst = fmax(worst, fabs(q - t));
+    return floor_to_i32(t);
+}
+
+__device__ __forceinline__ void covered_index(const SourceF64& s, const double* y, int* i, double& worst)
+{
+#pragma unroll
+    for (int c = 0; c < 3; ++c) i[c] = near_axis_f64(y[c], s.inv[c], s.obh[c], worst);
+}
+
 // floor(x) as an int in one instruction (v_cvt_flr_i32_f32 rounds toward
 // -infinity while it converts).  Equal to (int)floorf(x) for finite x in the
 // int range; beyond it the result saturates to INT_MIN or INT_MAX, which the
@@ -503,6 +527,28 @@ template <bool LEVELS = false>
 __device__ __forceinline__ float grid_keep_f32(const SourceF32& s, const GridProbe& p)
 {
     return probe_keep<LEVELS>(s, p);
+}
+
+__device__ __forceinline__ void covered_index(const SourceF32& s, const float* y, int* i, float&)
+{
+#pragma unroll
+    for (int c = 0; c < 3; ++c) i[c] = axis_f32(y[c], s.inv[c], s.ob[c]);
+}
+
+// A grid's values (or levels) behind a buffer descriptor: raw addressing by
+// bytes, reads at or past n_bytes return 0.  The host takes a covering loop
+// only for grids below 2^32 bytes.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t grid_buffer(const void* p, uint32_t n_bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)n_bytes, 0x00020000);
+}
+
+// The flat index of unclamped indices, modulo 2^32 (each product from 24-bit
+// factors: the host takes a covering loop only for layers below 2^24 voxels).
+template <class Src>
+__device__ __forceinline__ uint32_t covered_flat(const Src& s, const int* i)
+{
+    return __umul24((uint32_t)i[2], s.nxy) + (__umul24((uint32_t)i[1], (uint32_t)s.n[0]) + (uint32_t)i[0]);
 }
 
 // ---------------------------------------------------------------------------

@@ -25,6 +25,13 @@ struct SourceF64 {
     int32_t n_prisms;
     int32_t n_spheres;
     uint32_t nxy;              // n[0] n[1], the voxels of one layer
+    // covering loops (fk_walk.hip): points strictly between these bounds lie
+    // strictly inside the box and in the grid; obh = -origin / spacing - 1/2;
+    // near: the lookup's distance from 1/2 up to which rounding cannot change
+    // the voxel
+    double in_lo[3], in_hi[3];
+    double obh[3];
+    double near;
     double prisms[FK_MAX_PRISMS][7];
     double spheres[FK_MAX_SPHERES][5];
 };
@@ -41,6 +48,7 @@ struct SourceF32 {
     int32_t n_prisms;
     int32_t n_spheres;
     int32_t pad0;
+    float in_lo[3], in_hi[3];  // covering loops, as SourceF64's
     float prisms[FK_MAX_PRISMS][7];
     float spheres[FK_MAX_SPHERES][5];
 };
@@ -161,8 +169,10 @@ struct ReduceArgs {
 // by these global numbers (records from the launch's first task).
 struct BatchDesc {
     WalkCommon c;              // queue, exits, steps, n_tasks, task0 unused
-    SourceF64 s64;
-    SourceF32 s32;
+    union {                    // the batch's precision has one of them
+        SourceF64 s64;
+        SourceF32 s32;
+    };
     BoundaryArgs bc;
     fk_stat* out;              // this problem's first station result
     int64_t n_chunks;
@@ -223,9 +233,9 @@ hipError_t launch_zero_queue(unsigned long long* queue, hipStream_t stream, uint
 constexpr int64_t kAdjDenseVoxels = 32768;
 constexpr int64_t kAdjDenseMaxStations = 65536;
 constexpr int kAdjDenseBlock = 1024;
-hipError_t launch_walk_f64(const WalkArgsF64& a, const LaunchCfg& cfg, hipStream_t stream, bool adjoint = false,
-                           bool dense = false);
-hipError_t launch_walk_f32(const WalkArgsF32& a, bool kahan, const LaunchCfg& cfg, hipStream_t stream,
+hipError_t launch_walk_f64(const WalkArgsF64& a, const LaunchCfg& cfg, hipStream_t stream, int loop,
+                           bool adjoint = false, bool dense = false);
+hipError_t launch_walk_f32(const WalkArgsF32& a, bool kahan, const LaunchCfg& cfg, hipStream_t stream, int loop,
                            bool adjoint = false, bool dense = false);
 // Adjoint helpers: zero the count array; combine counts into the
 // vector-Jacobian product grad_rho[v] = sum_s coef_s * counts[s][v].
@@ -235,8 +245,9 @@ hipError_t launch_adjoint_combine(const int64_t* counts, int64_t n_stations, int
 // The chunk partials of pairs a.q0 .. a.q0 + n_pairs - 1; then, when
 // finish is set, every station's result from all its partials.
 hipError_t launch_reduce(const ReduceArgs& a, int64_t n_pairs, bool finish, hipStream_t stream);
-// loop: 0 box stepping loop, 1 with the ball exit test, 2 with the
-// Brownian-bridge test too
+// loop: the stepping loop (loop_kind in fk_api.cpp): 0 box, 1 with the ball
+// exit test, 2 with the Brownian-bridge test too; plus 4 with a voxel grid, 8
+// for a grid by levels, 16 where the grids cover their boxes
 hipError_t walk_occupancy(int precision, int block, int* blocks_per_cu, int loop = 0, bool adjoint = false,
                           bool dense = false);
 hipError_t launch_stream_blocks(const uint32_t* ctr, int64_t n, uint32_t key0, uint32_t key1, uint32_t* words,

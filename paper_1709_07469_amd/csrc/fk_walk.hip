@@ -954,121 +954,136 @@ struct Walker {
 // Shared drain rounds.  A lone walk stepping in its own lane issues every
 // instruction of a step -- some 60 of them, 5 cycles each with one wavefront
 // per SIMD -- for one step's worth of work.  Of a step only the move
-// x + sqrt(dt) z and the trapezoid sum depend on the step before; densities
-// and exit tests do not.  So in a round with at most kCoopLive live walks
-//   1. the chain of moves runs in three lanes per walk, one per axis, each
-//      replacing its normals in LDS by the positions they lead to;
+// x + sqrt(dt) z and the sum of densities depend on the step before; densities
+// and exit tests do not.  So in a round with at most kCoopLive live walks of
+// one problem
+//   1. the chain of moves runs in one lane per walk and axis, which replaces
+//      its row of normals in LDS by the positions they lead to (rows, so that
+//      16 bytes go with one LDS instruction: a move is one fused multiply-add
+//      and 0.5 (FP32) or 1 (FP64) LDS instructions);
 //   2. all 64 lanes take densities and exit tests of the round's points, up
 //      to MACRO points each, all grid loads in flight together;
-//   3. the lane that holds a walk adds its densities in step order, up
-//      to the first point that ends it (nothing to add when every density of
-//      the round is zero).
+//   3. the walks' densities are added in step order, up to the first point
+//      that ends a walk: only those that are not zero, one at a time from the
+//      lane that has it, or all of them from LDS where most are not.
 // The arithmetic of every step and its order are those of a macro-step, so a
 // walk's record does not depend on the rounds it ran in.
-// With more live walks step 1 would need more than a wavefront's lanes, and
-// the live lanes step through the buffer themselves.
-// Measured with the even shares of Queue::cap, before -> after: 8 stations x
-// 250 walks in FP64 1329 -> 229 us (a call returning host arrays); Table 1's
-// cells Delta t = 0.01, N = 5120: 6.67 -> 4.24 ms, and 0.001, N = 25600:
-// 129 -> 106 ms; its g_z with the bridge test, mixed, N = 2048: 7.17 -> 2.90 ms.
-constexpr int kCoopLive = 21;     // 3 lanes per walk
+// Measured, with the even shares of Queue::cap, against lanes stepping alone:
+// a lone walk 213 -> 38 ns a step in FP64, 175 to 214 -> 22 to 30 ns mixed;
+// 8 stations x 250 walks in FP64 1329 -> 173 us (a call returning host
+// arrays); Table 1's cells Delta t = 0.01, N = 5120: 6.67 -> 3.47 ms, and
+// 0.001, N = 25600 (with the FP64 normals): 129 -> 84.5 ms.
+constexpr int kCoopLive = 21;     // the chains fill a wavefront
 
+// A wavefront's LDS in a shared round.  Row (axis c, walk w) starts at
+// (c m + w) pitch, pitch = the round's steps and 16 bytes (so that rows start
+// in different banks); kRow holds the m rows of an axis for every m.
 template <bool F64>
 struct CoopRound {
-    typename Prec<F64>::T dens[64 * Prec<F64>::kMacro];   // density at step s of walk w: dens[s * m + w]
-    int end[kCoopLive + 1];                               // first step that ends walk w
-    int how[kCoopLive + 1];                               // and how (Walker::steps)
+    using T = typename Prec<F64>::T;
+    static constexpr int kV = 16 / (int)sizeof(T);        // elements per 16 bytes
+    static constexpr int kRow = 96 * Prec<F64>::kMacro;   // most m (macros MACRO + kV): 32 walks of 2 macro-steps
+    alignas(16) T pos[3 * kRow];
+    alignas(16) T dens[kRow];
+    int end[kCoopLive];           // first step that ends walk w
+    int how[kCoopLive];           // and how (Walker::steps)
+};
+
+template <class T>
+struct alignas(16) Quad {
+    T v[16 / sizeof(T)];
 };
 
 // One shared round: m live walks (walk w is held by lane lanes[w]; rank is w
 // in the lanes that hold one), `macros` macro-steps each, whose normals are
-// in zb (normal e of walk w at ((e / NPB) * m + w) * NPB + e % NPB).  P is the
-// live walks' problem.
+// in R.pos.  P is the live walks' problem.
 template <bool F64, bool KAHAN, int LOOP>
 __device__ __forceinline__ void coop_round(Walker<F64, KAHAN, false, LOOP>& W, const LaneProblem<F64>& P,
-                                           const typename Prec<F64>::Src& src, typename Prec<F64>::T* zb,
-                                           CoopRound<F64>& R, const int* lanes, int m, int macros, int rank)
+                                           const typename Prec<F64>::Src& src, CoopRound<F64>& R, const int* lanes,
+                                           int m, int macros, int rank)
 {
     using T = typename Prec<F64>::T;
-    constexpr int NPB = Prec<F64>::kNormals;
     constexpr int MACRO = Prec<F64>::kMacro;
+    constexpr int V = CoopRound<F64>::kV;
     const int lane = (int)__lane_id();
-    const int L = macros * MACRO;                 // steps per walk
-    const int over = 65536 / m + 1;               // t / m = t * over >> 16 for t < 256
-    auto at = [&](int s, int c, int w) {
-        const int e = 3 * s + c;
-        return ((e / NPB) * m + w) * NPB + e % NPB;
-    };
+    const int L = macros * MACRO;                 // steps per walk, a multiple of V
+    const int pitch = L + V;
+    const int over_m = 65536 / m + 1;             // q / m = q * over_m >> 16 for q < 128
+    const int over_L = 65536 / L + 1;             // t / L = t * over_L >> 16 for t < 256
 
-    // 1. positions: lane c m + w moves axis c of walk w
-    {
-        const int c = (lane * over) >> 16, w = lane - c * m;
+    // 1. positions: chain q = c m + w moves axis c of walk w
+#pragma unroll 1
+    for (int q0 = 0; q0 < 3 * m; q0 += 64) {
+        const int q = q0 + lane;
+        const int c = (q * over_m) >> 16, w = q - c * m;
         const int from = lanes[w];
-        const T q0 = __shfl(W.x0, from), q1 = __shfl(W.x1, from), q2 = __shfl(W.x2, from);
+        const T s0 = __shfl(W.x0, from), s1 = __shfl(W.x1, from), s2 = __shfl(W.x2, from);
         if (c < 3) {
-            T p = c == 0 ? q0 : c == 1 ? q1 : q2;
-            int off[MACRO];
-#pragma unroll
-            for (int i = 0; i < MACRO; ++i) off[i] = at(i, c, w);
-            const int stride = 3 * m * NPB;       // a macro-step's normals
-            constexpr int J = 8 / MACRO;          // macro-steps per batch of 8 steps
-            T z[8];
+            T p = c == 0 ? s0 : c == 1 ? s1 : s2;
+            Quad<T>* row = reinterpret_cast<Quad<T>*>(R.pos + q * pitch);
+            constexpr int J = 8 / V;              // a batch of 8 steps
+            const int n = L / V;
+            Quad<T> z[J];
             int j = 0;
-            if (J <= macros) {
+            if (J <= n) {
 #pragma unroll
-                for (int i = 0; i < 8; ++i) z[i] = zb[off[i % MACRO] + (i / MACRO) * stride];
+                for (int k = 0; k < J; ++k) z[k] = row[k];
             }
-            for (; j + J <= macros; j += J) {
+            for (; j + J <= n; j += J) {
                 // the next batch's loads are in flight while this one's chain runs
-                T zn[8] = {};
-                if (j + 2 * J <= macros) {
+                Quad<T> next[J] = {};
+                if (j + 2 * J <= n) {
 #pragma unroll
-                    for (int i = 0; i < 8; ++i) zn[i] = zb[off[i % MACRO] + (j + J + i / MACRO) * stride];
+                    for (int k = 0; k < J; ++k) next[k] = row[j + J + k];
                 }
 #pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    p = Prec<F64>::fmat(P.sdt, z[i], p);
-                    zb[off[i % MACRO] + (j + i / MACRO) * stride] = p;
+                for (int k = 0; k < J; ++k) {
+#pragma unroll
+                    for (int e = 0; e < V; ++e) z[k].v[e] = p = Prec<F64>::fmat(P.sdt, z[k].v[e], p);
+                    row[j + k] = z[k];
                 }
 #pragma unroll
-                for (int i = 0; i < 8; ++i) z[i] = zn[i];
+                for (int k = 0; k < J; ++k) z[k] = next[k];
             }
-            for (; j < macros; ++j)
+            for (; j < n; ++j) {
+                Quad<T> t = row[j];
 #pragma unroll
-                for (int i = 0; i < MACRO; ++i) {
-                    const int o = off[i] + j * stride;
-                    p = Prec<F64>::fmat(P.sdt, zb[o], p);
-                    zb[o] = p;
-                }
+                for (int e = 0; e < V; ++e) t.v[e] = p = Prec<F64>::fmat(P.sdt, t.v[e], p);
+                row[j] = t;
+            }
         }
-        if (lane < m) R.end[lane] = L;
     }
+    if (lane < m) R.end[lane] = L;
     wave_sync_lds();
 
-    // 2. densities and exit tests: point t = s m + w in lane t mod 64
+    // 2. densities and exit tests: point t = w L + s in lane t mod 64
+    auto at = [&](int c, int w, int s) { return (c * m + w) * pitch + s; };
     T y[3 * MACRO], rn[MACRO];
+    int ws[MACRO], ss[MACRO];
 #pragma unroll
     for (int i = 0; i < MACRO; ++i) {
-        int t = lane + 64 * i;
-        if (t >= L * m) t = lane < m ? lane : 0;  // no point: any other
-        const int s = (t * over) >> 16, w = t - s * m;
+        const int t = lane + 64 * i < L * m ? lane + 64 * i : 0;    // no point: any other
+        ws[i] = (t * over_L) >> 16;
+        ss[i] = t - ws[i] * L;
 #pragma unroll
-        for (int c = 0; c < 3; ++c) y[3 * i + c] = zb[at(s, c, w)];
+        for (int c = 0; c < 3; ++c) y[3 * i + c] = R.pos[at(c, ws[i], ss[i])];
     }
     Walker<F64, KAHAN, false, LOOP>::template densities<MACRO>(src, y, rn);
-    bool some = false, mass = false;
+    bool some = false;
     uint32_t ends = 0;                            // bit i: point i ends its walk
     int hows[MACRO];
+    uint64_t mass[MACRO];                         // lanes whose point i has a density
+    int n_mass = 0;
 #pragma unroll
     for (int i = 0; i < MACRO; ++i) {
-        const int t = lane + 64 * i;
-        const bool valid = t < L * m;
-        const int s = (t * over) >> 16, w = valid ? t - s * m : 0;
+        const bool valid = lane + 64 * i < L * m;
+        const int w = ws[i], s = ss[i];
         const int from = lanes[w];
         const uint32_t nw = (uint32_t)__shfl((int)W.n, from);
         const T y0 = y[3 * i], y1 = y[3 * i + 1], y2 = y[3 * i + 2];
-        if (valid) R.dens[t] = rn[i];
-        mass = mass | (valid & !(rn[i] == T(0)));
+        if (valid) R.dens[w * pitch + s] = rn[i];
+        mass[i] = __builtin_amdgcn_ballot_w64(valid & !(rn[i] == T(0)));
+        n_mass += __popcll(mass[i]);
         T d2;
         const bool out = Walker<F64, KAHAN, false, LOOP>::leaves(P, y0, y1, y2, d2);
         int stop = -1;
@@ -1077,9 +1092,9 @@ __device__ __forceinline__ void coop_round(Walker<F64, KAHAN, false, LOOP>& W, c
             T a0 = __shfl(W.x0, from), a1 = __shfl(W.x1, from), a2 = __shfl(W.x2, from);
             if (P.bridge && valid && !out) {
                 if (s > 0) {
-                    a0 = zb[at(s - 1, 0, w)];
-                    a1 = zb[at(s - 1, 1, w)];
-                    a2 = zb[at(s - 1, 2, w)];
+                    a0 = R.pos[at(0, w, s - 1)];
+                    a1 = R.pos[at(1, w, s - 1)];
+                    a2 = R.pos[at(2, w, s - 1)];
                 }
                 const T da = P.ball ? dist2(a0, a1, a2, P.lo0, P.lo1, P.lo2) : T(0);
                 if (!(W.deep_inside(P, a0, a1, a2, da) && W.deep_inside(P, y0, y1, y2, d2)))
@@ -1094,46 +1109,54 @@ __device__ __forceinline__ void coop_round(Walker<F64, KAHAN, false, LOOP>& W, c
         }
         some = some | end;
     }
-    const bool any_mass = __ballot(mass) != 0ull;
-    const bool any_end = __ballot(some) != 0ull;
+    const bool any_end = __builtin_amdgcn_ballot_w64(some) != 0ull;
     wave_sync_lds();
     if (any_end) {
 #pragma unroll
-        for (int i = 0; i < MACRO; ++i) {
-            if (ends & (1u << i)) {
-                const int t = lane + 64 * i;
-                const int s = (t * over) >> 16, w = t - s * m;
-                if (R.end[w] == s) R.how[w] = hows[i];
-            }
-        }
+        for (int i = 0; i < MACRO; ++i)
+            if ((ends & (1u << i)) && R.end[ws[i]] == ss[i]) R.how[ws[i]] = hows[i];
         wave_sync_lds();
     }
 
     // 3. the walks' sums and ends
-    if (W.active) {
-        const int f = any_end ? R.end[rank] : L;
-        const int taken = f < L ? f + 1 : L;
-        // a sum of zeros leaves an uncompensated sum as it is
-        if (KAHAN || any_mass) {
-            for (int s = 0; s < taken; s += 8) {
-                T d[8];
+    const int f = any_end && W.active ? R.end[rank] : L;
+    const int taken = f < L ? f + 1 : L;
+    // Adding a zero leaves an uncompensated sum as it is.  One density costs
+    // some 8 instructions from its lane, a step of every walk 3 from LDS.
+    if (!KAHAN && 8 * n_mass <= 3 * L) {
 #pragma unroll
-                for (int i = 0; i < 8; ++i) d[i] = R.dens[(s + i < L ? s + i : L - 1) * m + rank];
-#pragma unroll
-                for (int i = 0; i < 8; ++i)
-                    if (s + i < taken) W.add_density(s + i == f ? T(0.5) * d[i] : d[i]);
+        for (int i = 0; i < MACRO; ++i)
+            for (uint64_t left = mass[i]; left != 0ull; left &= left - 1ull) {
+                const int b = __ffsll((unsigned long long)left) - 1;
+                const T r = lane_value(rn[i], b);
+                const int w = __builtin_amdgcn_readlane(ws[i], b), s = __builtin_amdgcn_readlane(ss[i], b);
+                if (W.active & (rank == w) & (s <= f)) W.add_density(s == f ? T(0.5) * r : r);
             }
+    } else if (W.active) {
+        const T* row = R.dens + rank * pitch;
+        const int whole = f < L ? f : L;          // densities of full weight
+        int s = 0;
+        for (; s + 8 <= whole; s += 8) {
+            Quad<T> d[8 / V];
+#pragma unroll
+            for (int k = 0; k < 8 / V; ++k) d[k] = *reinterpret_cast<const Quad<T>*>(row + s + k * V);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) W.add_density(d[e / V].v[e % V]);
         }
+        for (; s < whole; ++s) W.add_density(row[s]);
+        if (f < L) W.add_density(T(0.5) * row[f]);
+    }
+    if (W.active) {
         W.n += (uint32_t)taken;
         W.k += (uint32_t)(3 * macros);
-        const int l = f < L ? f : L - 1;          // the last point reached
-        const T e0 = zb[at(l, 0, rank)], e1 = zb[at(l, 1, rank)], e2 = zb[at(l, 2, rank)];
+        const int l = taken - 1;                  // the last point reached
+        const T e0 = R.pos[at(0, rank, l)], e1 = R.pos[at(1, rank, l)], e2 = R.pos[at(2, rank, l)];
         if (f < L) {
             T a0 = W.x0, a1 = W.x1, a2 = W.x2;
             if (f > 0) {
-                a0 = zb[at(f - 1, 0, rank)];
-                a1 = zb[at(f - 1, 1, rank)];
-                a2 = zb[at(f - 1, 2, rank)];
+                a0 = R.pos[at(0, rank, f - 1)];
+                a1 = R.pos[at(1, rank, f - 1)];
+                a2 = R.pos[at(2, rank, f - 1)];
             }
             W.finish_at(P, a0, a1, a2, e0, e1, e2, R.how[rank]);
         } else {
@@ -1170,8 +1193,16 @@ __device__ __forceinline__ void walk_body(const Args& A)
     static_assert(!DENSE || (ADJ && !BATCH), "dense tables are the adjoint's");
 
     __shared__ int tail_lane[TAIL_WAVES][64];
-    __shared__ T tail_z[TAIL_WAVES][3 * 64][NPB];
-    __shared__ CoopRound<F64> coop[DRAIN && !ADJ ? kMaxWaves : 1];
+    // a drain round's normals: block slots of NPB, or a shared round's rows
+    // (the adjoint's blocks have LDS for half as many slots beside its table)
+    constexpr int kSlots = ADJ ? 192 : 384;
+    struct Slots {
+        Quad<T> z[kSlots];
+    };
+    static_assert(NPB == 16 / (int)sizeof(T), "a slot is 16 bytes");
+    using Tail = typename std::conditional<ADJ, Slots, CoopRound<F64>>::type;
+    static_assert(sizeof(Tail) >= sizeof(Slots), "the slots of a round that is not shared lie in its LDS");
+    __shared__ Tail tail[TAIL_WAVES];
     const BmTables* bmt = nullptr;
     if constexpr (F64) {
         BmTables* t = bm_tables();
@@ -1388,20 +1419,31 @@ __device__ __forceinline__ void walk_body(const Args& A)
             // ---- drain round: the queue is empty, or the launch gives no
             // wavefront more walks than these, so every lane generates Philox
             // blocks for the live walks of its wavefront (block slot
-            // g = r * m + w holds block r of live walk w): 192 slots, or 128
-            // where 33 to 42 live walks would leave a third of them unused.
-            // Each live walk then takes B / 3 macro-steps from LDS.
+            // g = r * m + w holds block r of live walk w), for as many
+            // macro-steps of each as the slots hold: of the lanes' passes at
+            // most a fifth is then unused, however many walks are live.
             const int rank = __popcll(live & __lanemask_lt());
             if (W.active) tail_lane[wave][rank] = lane;
             wave_sync_lds();
-            const int macros = m > 32 ? 1 : 64 / m;    // macro-steps per live walk this round
+            // shared: few enough live walks, all of one problem
+            const int first = __ffsll((unsigned long long)live) - 1;
+            bool shared = !ADJ && m <= kCoopLive;
+            if constexpr (!ADJ && BATCH) {
+                const uint64_t pc = lane_u64((uint64_t)P.C, first);
+                shared = shared && __builtin_amdgcn_ballot_w64(W.active && (uint64_t)P.C != pc) == 0ull;
+            }
+            // macro-steps per live walk this round
+            const int macros = shared ? 64 / m : kSlots / (3 * m);
             const int B = 3 * macros;                  // blocks per live walk
-            const int passes = m > 32 && m <= 42 ? 2 : 3;
+            const int passes = (B * m + 63) / 64;
+            T* const slots = reinterpret_cast<T*>(&tail[wave]);
+            const int over = 65536 / m + 1;            // g / m = g * over >> 16 for g < 384
+            const int pitch = macros * MACRO + CoopRound<F64>::kV;
 #pragma unroll 1
             for (int i = 0; i < passes; ++i) {
                 const int g = lane + 64 * i;
-                const int w = g % m;
-                const int r = g / m;
+                const int r = (g * over) >> 16;
+                const int w = g - r * m;
                 const int src = tail_lane[wave][w];
                 const uint32_t ks = (uint32_t)__shfl((int)W.k, src);
                 const uint32_t ps = (uint32_t)__shfl((int)W.pctr, src);
@@ -1419,34 +1461,35 @@ __device__ __forceinline__ void walk_body(const Args& A)
                     const Block bl = philox10(ks + (uint32_t)r, ps, ss, pid, key0, key1);
                     T z[NPB];
                     Prec<F64>::normals(bl, z, bmt);
+                    if (shared) {
+                        // normal e = NPB r + j of walk w: step e / 3, axis e mod 3
+                        int s = (NPB * r * 21846) >> 16, c = NPB * r - 3 * s;
 #pragma unroll
-                    for (int j = 0; j < NPB; ++j) tail_z[wave][g][j] = z[j];
+                        for (int j = 0; j < NPB; ++j) {
+                            slots[(c * m + w) * pitch + s] = z[j];
+                            s += c == 2;
+                            c = c == 2 ? 0 : c + 1;
+                        }
+                    } else {
+#pragma unroll
+                        for (int j = 0; j < NPB; ++j) slots[g * NPB + j] = z[j];
+                    }
                 }
             }
             wave_sync_lds();
             if constexpr (!ADJ) {
-                if (m <= kCoopLive) {
-                    // the problem of the first live walk; the round is shared
-                    // only when all live walks belong to it
-                    const int first = __ffsll((unsigned long long)live) - 1;
+                if (shared) {
                     LaneProblem<F64> PE = P;
-                    bool same = true;
-                    if constexpr (BATCH) {
-                        const uint64_t pc = lane_u64((uint64_t)P.C, first);
-                        same = __ballot(W.active && (uint64_t)P.C != pc) == 0ull;
-                        if (same) PE.from_lane(P, first, !UKEY);
-                    }
-                    if (same) {
-                        const typename Prec<F64>::Src* sp;
-                        if constexpr (BATCH && !SHARED)
-                            sp = (const typename Prec<F64>::Src*)(const __attribute__((address_space(4)))
-                                                                  typename Prec<F64>::Src*)(uint64_t)PE.src;
-                        else
-                            sp = &source();
-                        coop_round(W, PE, *sp, &tail_z[wave][0][0], coop[wave], tail_lane[wave], m, macros, rank);
-                        wave_sync_lds();
-                        continue;
-                    }
+                    const typename Prec<F64>::Src* sp;
+                    if constexpr (BATCH) PE.from_lane(P, first, !UKEY);
+                    if constexpr (BATCH && !SHARED)
+                        sp = (const typename Prec<F64>::Src*)(const __attribute__((address_space(4)))
+                                                              typename Prec<F64>::Src*)(uint64_t)PE.src;
+                    else
+                        sp = &source();
+                    coop_round(W, PE, *sp, tail[wave], tail_lane[wave], m, macros, rank);
+                    wave_sync_lds();
+                    continue;
                 }
             }
             if (W.active) {
@@ -1456,9 +1499,10 @@ __device__ __forceinline__ void walk_body(const Args& A)
                 for (int s0 = 0; s0 < n_steps && !done; s0 += MACRO) {
                     T zz[3 * MACRO];
 #pragma unroll
-                    for (int c = 0; c < 3 * MACRO; ++c) {
-                        const int q = 3 * s0 + c;
-                        zz[c] = tail_z[wave][(q / NPB) * m + rank][q % NPB];
+                    for (int b = 0; b < 3; ++b) {
+                        const Quad<T> q = reinterpret_cast<const Quad<T>*>(slots)[(3 * (s0 / MACRO) + b) * m + rank];
+#pragma unroll
+                        for (int j = 0; j < NPB; ++j) zz[NPB * b + j] = q.v[j];
                     }
                     int at = 0;
                     W.advance(P, zz);

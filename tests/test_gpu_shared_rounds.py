@@ -1,7 +1,7 @@
 """GPU: launches that give every wavefront a few walks run them in shared
 drain rounds; the number of live walks decides how a round is divided (3 lanes
-per walk up to 21 walks, the walks' own lanes beyond, two generation passes
-instead of three for 33 to 42).  At the edges of those ranges every walk's
+per walk up to 21 walks, the walks' own lanes beyond, and as many macro-steps as
+the block slots hold).  At the edges of those ranges every walk's
 record must equal the oracle's in FP64 (1e-12 of the mean |u|, step counts
 exactly), and in every precision, bit for bit, what a full launch records.
 """

@@ -648,6 +648,27 @@ fk_status plan_launch(int precision, int64_t n_tasks, fk::LaunchCfg* cfg, int* l
     return st;
 }
 
+// Blocks per (station, chunk) pair that form the samples of a launch's
+// reduction before it (1: it forms them itself); largest: the walks of its
+// largest pair.  A block takes a pair's up to 8192 paths 256 walks at a time;
+// where the data are prisms', whose evaluation is nearly all of that, and the
+// pairs fill few of the chip's wavefronts, up to 8 blocks per compute unit
+// share them instead: 78 pairs of 2 x 8192 walks and 5 prisms took 935 us in
+// one pass, 220 + 29 us in two.  Not for pairs of fewer than 8 walks a lane,
+// where the second launch costs what it saves: a batch of 474 pairs of up to 7
+// walks a lane took 1167 us in one pass and 1173 in two.
+int sample_parts(bool prisms, int64_t pairs, int64_t largest)
+{
+    int dev = 0;
+    if (!prisms || pairs < 1 || hipGetDevice(&dev) != hipSuccess) return 1;
+    const int64_t want = 8 * (int64_t)compute_units(dev) / pairs;       // blocks per pair
+    const int64_t most = (largest + 255) / 256;                         // with a walk per lane
+    return want < 2 || most < 8 ? 1 : (int)std::min(want, most);
+}
+
+// The walks of the shape's largest (station, chunk) pair.
+int64_t pair_walks(const Shape& p) { return std::min<int64_t>(p.N, kChunk) * p.npair; }
+
 // Checks every argument of a single solve except the workspace.
 fk_status check_solve(int32_t kind, const double* stations, int64_t n_stations, const fk_box* box,
                       const fk_source* src, const fk_boundary* bc, const fk_params* p, const fk_stat* out)
@@ -734,12 +755,13 @@ fk_status run_solve(int32_t kind, const double* stations, int64_t n_stations, co
         if (e != hipSuccess) return fail(FK_EDEVICE, "walk launch failed: %s", hipGetErrorString(e));
         R.q0 = sl.q0;
         R.task0 = sl.t0;
-        e = fk::launch_reduce(R, sl.q1 - sl.q0, false, stream);
+        const int64_t pairs = sl.q1 - sl.q0;
+        e = fk::launch_reduce(R, pairs, sample_parts(bc->kind == FK_BC_PRISMS, pairs, pair_walks(shapes[0])), false, stream);
         if (e != hipSuccess) return fail(FK_EDEVICE, "reduction launch failed: %s", hipGetErrorString(e));
         return FK_OK;
     });
     if (st != FK_OK) return st;
-    const hipError_t e = fk::launch_reduce(R, 0, true, stream);
+    const hipError_t e = fk::launch_reduce(R, 0, 1, true, stream);
     if (e != hipSuccess) return fail(FK_EDEVICE, "reduction launch failed: %s", hipGetErrorString(e));
     return FK_OK;
 }
@@ -950,6 +972,14 @@ fk_status solve_batch(const fk_problem* probs, int32_t n, fk_stat* out, void* wo
     A.chunk = kChunk;
 
     bool first = true;
+    bool prism_data = false, chunked = false;      // any problem's data; stations of several chunks
+    int64_t largest = 0;                           // pair of a problem with prism data
+    for (int32_t m = 0; m < n; ++m) {
+        chunked = chunked || BL.shapes[m].n_chunks > 1;
+        if (probs[m].bc.kind != FK_BC_PRISMS) continue;
+        prism_data = true;
+        largest = std::max(largest, pair_walks(BL.shapes[m]));
+    }
     st = for_each_slice(BL.shapes, BL.held, [&](const Slice& sl) -> fk_status {
         hipError_t le = hipSuccess;
         if (!first) le = fk::launch_zero_queue(queue, stream);
@@ -973,12 +1003,13 @@ fk_status solve_batch(const fk_problem* probs, int32_t n, fk_stat* out, void* wo
         le = fk::launch_batch_walk(A, cfg, stream, slice_loop, shared);
         if (timed) timing_end(ev, stream);
         if (le != hipSuccess) return fail(FK_EDEVICE, "batch walk launch failed: %s", hipGetErrorString(le));
-        le = fk::launch_batch_chunks(A, sl.q1 - sl.q0, stream);
+        const int64_t pairs = sl.q1 - sl.q0;
+        le = fk::launch_batch_chunks(A, pairs, sample_parts(prism_data, pairs, largest), stream);
         if (le != hipSuccess) return fail(FK_EDEVICE, "batch reduction launch failed: %s", hipGetErrorString(le));
         return FK_OK;
     });
     if (st != FK_OK) return st;
-    e = fk::launch_batch_stations(A, BL.n_stations, stream);
+    if (chunked) e = fk::launch_batch_stations(A, BL.n_stations, stream);
     if (e != hipSuccess) return fail(FK_EDEVICE, "batch reduction launch failed: %s", hipGetErrorString(e));
     return FK_OK;
 }

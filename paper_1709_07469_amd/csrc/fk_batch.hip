@@ -30,8 +30,10 @@ __global__ void write_words_kernel(uint64_t* dst, const Words w, int n)
 // ---------------------------------------------------------------------------
 // Batched reduction: the pairs of all problems in one launch; block b takes
 // global pair q0 + b and finds its problem by binary search over the pair
-// prefix sums.  Same arithmetic and order as the single-problem reduction.
+// prefix sums.  Same arithmetic, order and passes as the single-problem
+// reduction.
 // ---------------------------------------------------------------------------
+template <int PASS>
 __global__ void __launch_bounds__(kReduceBlock) batch_chunk_kernel(const BatchArgs B)
 {
     const int64_t gq = B.q0 + blockIdx.x;
@@ -45,20 +47,22 @@ __global__ void __launch_bounds__(kReduceBlock) batch_chunk_kernel(const BatchAr
     const int64_t i1 = (i0 + B.chunk < N) ? i0 + B.chunk : N;
 
     DataTables tb{nullptr, nullptr};
-    if (D.bc.kind == FK_BC_PRISMS) tb = fill_data_tables();     // one problem per block: uniform
+    if (PASS != kFromSamples && D.bc.kind == FK_BC_PRISMS) tb = fill_data_tables();   // one problem per block: uniform
 
     const int64_t rec0 = B.task_off[m] + s * N * D.c.npair - B.task0;
     const PairSpan P{B.exits, B.steps, B.values ? B.values + B.task0 : nullptr, rec0, i0, i1, D.c.npair,
                      2.0 * D.c.h};
     auto data = [&](const ExitRecord& r) {
+        if (PASS == kFromSamples) return r.S;
         const double e[3] = {r.x, r.y, r.z};
         return boundary_value(D.bc, D.c.lo, D.c.hi, D.c.G, e, tb) - D.c.w * r.S;
     };
-    reduce_pair(P, data, B.partials + gq, B.status);
+    if constexpr (PASS == kSamples) sample_pair(P, data, blockIdx.y, gridDim.y);
+    else reduce_pair(P, data, B.partials + gq, B.status, D.n_chunks == 1 ? D.out + s : nullptr, N);
 }
 
 // Thread g handles station g of the concatenated station list (problems in
-// order, each problem's stations in order).
+// order, each problem's stations in order); those of one chunk are finished.
 __global__ void __launch_bounds__(64) batch_station_kernel(const BatchArgs B, int64_t n_total)
 {
     const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -70,6 +74,7 @@ __global__ void __launch_bounds__(64) batch_station_kernel(const BatchArgs B, in
         else hi = mid;
     }
     const BatchDesc& D = B.desc[lo];
+    if (D.n_chunks == 1) return;
     const int64_t s = g - D.station_base;
     D.out[s] = finish_station(B.partials + D.block_base + s * D.n_chunks, D.n_chunks, D.c.N);
 }
@@ -89,10 +94,18 @@ hipError_t launch_write_words(uint64_t* dst, const uint64_t* host_words, int64_t
     return hipSuccess;
 }
 
-hipError_t launch_batch_chunks(const BatchArgs& a, int64_t n_pairs, hipStream_t stream)
+hipError_t launch_batch_chunks(const BatchArgs& a, int64_t n_pairs, int parts, hipStream_t stream)
 {
     if (n_pairs <= 0) return hipSuccess;
-    hipLaunchKernelGGL(batch_chunk_kernel, dim3((unsigned)n_pairs), dim3(kReduceBlock), 0, stream, a);
+    if (parts > 1) {
+        hipLaunchKernelGGL(batch_chunk_kernel<kSamples>, dim3((unsigned)n_pairs, (unsigned)parts), dim3(kReduceBlock),
+                           0, stream, a);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(batch_chunk_kernel<kFromSamples>, dim3((unsigned)n_pairs), dim3(kReduceBlock), 0, stream, a);
+    } else {
+        hipLaunchKernelGGL(batch_chunk_kernel<kOnePass>, dim3((unsigned)n_pairs), dim3(kReduceBlock), 0, stream, a);
+    }
     return hipGetLastError();
 }
 

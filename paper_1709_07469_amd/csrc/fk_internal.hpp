@@ -141,7 +141,7 @@ struct Partial {
 // The reduction of the (station, chunk) pairs q0 .. q0 + gridDim - 1 (pair
 // q = s * n_chunks + c) whose walks' records start at task task0.
 struct ReduceArgs {
-    const ExitRecord* exits;
+    ExitRecord* exits;
     double* values;            // per-walk samples written here (record mode), or null
     const uint32_t* steps;
     Partial* partials;         // one per pair, all pairs of the solve
@@ -242,9 +242,10 @@ hipError_t launch_walk_f32(const WalkArgsF32& a, bool kahan, const LaunchCfg& cf
 hipError_t launch_fill_zero(int64_t* p, int64_t n, hipStream_t stream);
 hipError_t launch_adjoint_combine(const int64_t* counts, int64_t n_stations, int64_t nvox, const double* grad_out,
                                   const fk_stat* fwd, double scale, double* grad_rho, hipStream_t stream);
-// The chunk partials of pairs a.q0 .. a.q0 + n_pairs - 1; then, when
-// finish is set, every station's result from all its partials.
-hipError_t launch_reduce(const ReduceArgs& a, int64_t n_pairs, bool finish, hipStream_t stream);
+// The chunk partials of pairs a.q0 .. a.q0 + n_pairs - 1, with parts > 1 in two
+// passes, the first with that many blocks per pair; then, when finish is set,
+// every station's result from all its partials.
+hipError_t launch_reduce(const ReduceArgs& a, int64_t n_pairs, int parts, bool finish, hipStream_t stream);
 // loop: the stepping loop (loop_kind in fk_api.cpp): 0 box, 1 with the ball
 // exit test, 2 with the Brownian-bridge test too; plus 4 with a voxel grid, 8
 // for a grid by levels, 16 where the grids cover their boxes
@@ -258,7 +259,7 @@ hipError_t launch_stream_blocks(const uint32_t* ctr, int64_t n, uint32_t key0, u
 // and the batched reduction.
 hipError_t launch_write_words(uint64_t* dst, const uint64_t* host_words, int64_t n_words, hipStream_t stream);
 hipError_t launch_batch_walk(const BatchArgs& a, const LaunchCfg& cfg, hipStream_t stream, int loop, bool shared);
-hipError_t launch_batch_chunks(const BatchArgs& a, int64_t n_pairs, hipStream_t stream);
+hipError_t launch_batch_chunks(const BatchArgs& a, int64_t n_pairs, int parts, hipStream_t stream);
 hipError_t launch_batch_stations(const BatchArgs& a, int64_t n_stations, hipStream_t stream);
 hipError_t batch_occupancy(int precision, int block, int* blocks_per_cu, int loop = 0, bool shared = false,
                            bool ukey = false);

@@ -8,7 +8,8 @@
 // chunk) pair turns the pair's samples into a (count, mean, M2) partial in a
 // fixed order; a second kernel merges a station's partials in chunk order.
 // A bounded workspace runs the first kernel once per slice of pairs, as soon
-// as the slice's walks are done, and the second once at the end.
+// as the slice's walks are done, and the second once at the end.  Stations of
+// one chunk need no second kernel: the block of their pair writes their result.
 #include <hip/hip_runtime.h>
 
 #include "fk_stats.hpp"
@@ -17,6 +18,11 @@ namespace fk {
 
 namespace {
 
+// Bound by the evaluation of the Dirichlet data (24 corner terms a prism, FP64
+// vector arithmetic).  One block per pair leaves most of the chip idle where
+// pairs are few (sample_parts in fk_api.cpp): two passes then, the first with
+// several blocks per pair.
+template <int PASS>
 __global__ void __launch_bounds__(kReduceBlock) chunk_kernel(const ReduceArgs R)
 {
     const int64_t q = R.q0 + blockIdx.x;
@@ -26,14 +32,16 @@ __global__ void __launch_bounds__(kReduceBlock) chunk_kernel(const ReduceArgs R)
     const int64_t i1 = (i0 + R.chunk < R.N) ? i0 + R.chunk : R.N;
 
     DataTables tb{nullptr, nullptr};
-    if (R.bc.kind == FK_BC_PRISMS) tb = fill_data_tables();     // uniform: every thread takes it
+    if (PASS != kFromSamples && R.bc.kind == FK_BC_PRISMS) tb = fill_data_tables();   // uniform: every thread takes it
 
     const PairSpan P{R.exits, R.steps, R.values, s * R.N * R.npair - R.task0, i0, i1, R.npair, R.two_h};
     auto data = [&](const ExitRecord& r) {
+        if (PASS == kFromSamples) return r.S;
         const double e[3] = {r.x, r.y, r.z};
         return boundary_value(R.bc, R.lo, R.hi, R.G, e, tb) - R.w * r.S;
     };
-    reduce_pair(P, data, R.partials + q, R.status);
+    if constexpr (PASS == kSamples) sample_pair(P, data, blockIdx.y, gridDim.y);
+    else reduce_pair(P, data, R.partials + q, R.status, R.n_chunks == 1 ? R.out + s : nullptr, R.N);
 }
 
 __global__ void __launch_bounds__(64) station_kernel(const ReduceArgs R)
@@ -45,14 +53,22 @@ __global__ void __launch_bounds__(64) station_kernel(const ReduceArgs R)
 
 }  // namespace
 
-hipError_t launch_reduce(const ReduceArgs& a, int64_t n_pairs, bool finish, hipStream_t stream)
+hipError_t launch_reduce(const ReduceArgs& a, int64_t n_pairs, int parts, bool finish, hipStream_t stream)
 {
     if (n_pairs > 0) {
-        hipLaunchKernelGGL(chunk_kernel, dim3((unsigned)n_pairs), dim3(kReduceBlock), 0, stream, a);
+        if (parts > 1) {
+            hipLaunchKernelGGL(chunk_kernel<kSamples>, dim3((unsigned)n_pairs, (unsigned)parts), dim3(kReduceBlock), 0,
+                               stream, a);
+            const hipError_t e = hipGetLastError();
+            if (e != hipSuccess) return e;
+            hipLaunchKernelGGL(chunk_kernel<kFromSamples>, dim3((unsigned)n_pairs), dim3(kReduceBlock), 0, stream, a);
+        } else {
+            hipLaunchKernelGGL(chunk_kernel<kOnePass>, dim3((unsigned)n_pairs), dim3(kReduceBlock), 0, stream, a);
+        }
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    if (!finish) return hipSuccess;
+    if (!finish || a.n_chunks == 1) return hipSuccess;
     hipLaunchKernelGGL(station_kernel, dim3((unsigned)((a.n_stations + 63) / 64)), dim3(64), 0, stream, a);
     return hipGetLastError();
 }

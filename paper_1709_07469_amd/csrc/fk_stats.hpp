@@ -76,7 +76,7 @@ __device__ __forceinline__ int find_problem(const int64_t* off, int n, int64_t t
 // combine.  rec0 = (s N) npair - first task held, so local path i, walk w
 // is at rec0 + i npair + w.
 struct PairSpan {
-    const ExitRecord* exits;
+    ExitRecord* exits;
     const uint32_t* steps;
     double* values;           // per-walk samples written here; null: not kept
     int64_t rec0;
@@ -95,14 +95,33 @@ __device__ __forceinline__ double pair_sample(const PairSpan& P, int64_t j, uint
     return v;
 }
 
+// A reduction in two passes (sample_parts in fk_api.cpp): kSamples puts each
+// walk's sample in place of its record's sum, kFromSamples reduces those;
+// kOnePass forms the samples as it reduces.
+enum ReducePass { kOnePass = 0, kSamples = 1, kFromSamples = 2 };
+
+// Block `part` of the `parts` that share a pair's samples.
+template <class Data>
+__device__ __forceinline__ void sample_pair(const PairSpan& P, const Data& data, int part, int parts)
+{
+    const int64_t j1 = P.rec0 + P.i1 * P.npair;
+    for (int64_t j = P.rec0 + P.i0 * P.npair + part * kReduceBlock + (int)threadIdx.x; j < j1;
+         j += parts * kReduceBlock)
+        if ((P.steps[j] & kCapFlag) == 0) P.exits[j].S = data(P.exits[j]);
+}
+
 // Reduces one pair into *out with the whole block (kReduceBlock threads) and
 // ORs the anomaly flags of its walks into *status: FK_FLAG_TRUNCATED when a
 // walk was capped (max_steps, or a start point not strictly inside),
 // FK_FLAG_NONFINITE when an uncapped sample is not finite (a NaN or infinite
 // density, position or datum).  data(record) gives a walk's sample
-// u_p = g(x_e) - 2 pi G (dt/2) S.
+// u_p = g(x_e) - 2 pi G (dt/2) S.  A station of one chunk is complete with it:
+// station, if not null, gets its result (of N paths).
+__device__ __forceinline__ fk_stat finish_station(const Partial* parts, int64_t n_chunks, int64_t N);
+
 template <class Data>
-__device__ __forceinline__ void reduce_pair(const PairSpan& P, const Data& data, Partial* out, uint32_t* status)
+__device__ __forceinline__ void reduce_pair(const PairSpan& P, const Data& data, Partial* out, uint32_t* status,
+                                            fk_stat* station, int64_t N)
 {
     Acc a{0.0, 0.0, 0.0, 0, 0, 0};
     uint32_t flags = 0;
@@ -169,6 +188,7 @@ __device__ __forceinline__ void reduce_pair(const PairSpan& P, const Data& data,
         p.max_steps = t.max_steps;
         p.n_trunc = t.n_trunc;
         if (f) atomicOr(status, f);
+        if (station) *station = finish_station(&p, 1, N);
     }
 }
 

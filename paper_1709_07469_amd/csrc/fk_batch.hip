@@ -16,15 +16,13 @@ namespace fk {
 
 namespace {
 
-constexpr int kWords = 256;   // 2 KiB of payload per write launch
-
-struct Words {
-    uint64_t v[kWords];
-};
-
-__global__ void write_words_kernel(uint64_t* dst, const Words w, int n)
+// Wavefront w writes runs w, w + 4, ...
+__global__ void __launch_bounds__(256) write_runs_kernel(uint64_t* base, const WordRuns R)
 {
-    for (int i = threadIdx.x; i < n; i += blockDim.x) dst[i] = w.v[i];
+    for (int r = threadIdx.x >> 6; r < R.n_runs; r += 4) {
+        const int n = R.run[r].words, from = R.run[r].from;
+        for (int i = (int)__lane_id(); i < n; i += 64) base[R.run[r].at + i] = R.v[from + i];
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -81,17 +79,10 @@ __global__ void __launch_bounds__(64) batch_station_kernel(const BatchArgs B, in
 
 }  // namespace
 
-hipError_t launch_write_words(uint64_t* dst, const uint64_t* host_words, int64_t n_words, hipStream_t stream)
+hipError_t launch_write_runs(uint64_t* base, const WordRuns& runs, hipStream_t stream)
 {
-    for (int64_t at = 0; at < n_words; at += kWords) {
-        Words w;
-        const int n = (int)((n_words - at) < kWords ? (n_words - at) : kWords);
-        for (int i = 0; i < n; ++i) w.v[i] = host_words[at + i];
-        hipLaunchKernelGGL(write_words_kernel, dim3(1), dim3(256), 0, stream, dst + at, w, n);
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
+    hipLaunchKernelGGL(write_runs_kernel, dim3(1), dim3(256), 0, stream, base, runs);
+    return hipGetLastError();
 }
 
 hipError_t launch_batch_chunks(const BatchArgs& a, int64_t n_pairs, int parts, hipStream_t stream)

@@ -212,6 +212,20 @@ struct BatchArgs {
     SourceF32 src32;
 };
 
+// One launch's share of an upload: runs of words for base[run.at ..], their
+// values in order, within the 4 KB of arguments a launch may carry.
+struct WordRuns {
+    static constexpr int kWords = 440, kRuns = 32;
+    struct Run {
+        int64_t at;            // from `base`, in words
+        int16_t from, words;   // in v
+    };
+    uint64_t v[kWords];
+    Run run[kRuns];
+    int32_t n_runs, n_words;
+};
+static_assert(sizeof(WordRuns) <= 4080, "a launch's arguments");
+
 struct LaunchCfg {
     int block;
     int grid;
@@ -257,7 +271,7 @@ hipError_t launch_stream_blocks(const uint32_t* ctr, int64_t n, uint32_t key0, u
 // Batched solve: descriptor upload (by value through kernel arguments, so a
 // captured graph replays it), the persistent walk kernel over all problems,
 // and the batched reduction.
-hipError_t launch_write_words(uint64_t* dst, const uint64_t* host_words, int64_t n_words, hipStream_t stream);
+hipError_t launch_write_runs(uint64_t* base, const WordRuns& runs, hipStream_t stream);
 hipError_t launch_batch_walk(const BatchArgs& a, const LaunchCfg& cfg, hipStream_t stream, int loop, bool shared);
 hipError_t launch_batch_chunks(const BatchArgs& a, int64_t n_pairs, int parts, hipStream_t stream);
 hipError_t launch_batch_stations(const BatchArgs& a, int64_t n_stations, hipStream_t stream);

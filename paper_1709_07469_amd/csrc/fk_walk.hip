@@ -984,7 +984,8 @@ struct CoopRound {
     static constexpr int kV = 16 / (int)sizeof(T);        // elements per 16 bytes
     static constexpr int kRow = 96 * Prec<F64>::kMacro;   // most m (macros MACRO + kV): 32 walks of 2 macro-steps
     alignas(16) T pos[3 * kRow];
-    alignas(16) T dens[kRow];
+    static constexpr int kPad = 128 / (int)sizeof(T);     // read past a row's end (for_row)
+    alignas(16) T dens[kRow + kPad];
     int end[kCoopLive];           // first step that ends walk w
     int how[kCoopLive];           // and how (Walker::steps)
 };
@@ -993,6 +994,68 @@ template <class T>
 struct alignas(16) Quad {
     T v[16 / sizeof(T)];
 };
+
+// fma(s, z, p) in z's register: the compiler's choice, the form that adds to
+// p's, needs a copy for each position stored.
+__device__ __forceinline__ double fma_into(double z, double s, double p)
+{
+    double r;
+    asm("v_fma_f64 %0, %1, %2, %3" : "=v"(r) : "v"(s), "v"(z), "v"(p));
+    return r;
+}
+
+__device__ __forceinline__ float fma_into(float z, float s, float p)
+{
+    float r;
+    asm("v_fma_f32 %0, %1, %2, %3" : "=v"(r) : "v"(s), "v"(z), "v"(p));
+    return r;
+}
+
+// Reads the row's quads two batches of 64 bytes ahead of f(quad index, quad),
+// which is called on its n quads in order: a lone chain of additions then waits
+// for itself, not for the LDS.  Up to 128 bytes past the row are read, and not
+// used (CoopRound::kPad).
+template <bool F64, class T = typename Prec<F64>::T, class F>
+__device__ __forceinline__ void for_row(const Quad<T>* row, int n, F&& f)
+{
+    constexpr int J = 4;
+    Quad<T> a[J], b[J];
+#pragma unroll
+    for (int k = 0; k < J; ++k) a[k] = row[k];
+#pragma unroll
+    for (int k = 0; k < J; ++k) b[k] = row[J + k];
+    int j = 0;
+#pragma unroll 1
+    for (; j + 2 * J <= n; j += 2 * J) {
+#pragma unroll
+        for (int k = 0; k < J; ++k) f(j + k, a[k]);
+#pragma unroll
+        for (int k = 0; k < J; ++k) a[k] = row[j + 2 * J + k];
+#pragma unroll
+        for (int k = 0; k < J; ++k) f(j + J + k, b[k]);
+        __builtin_amdgcn_sched_barrier(0);        // moved up, the reads would need registers of their own, and copies
+#pragma unroll
+        for (int k = 0; k < J; ++k) b[k] = row[j + 3 * J + k];
+    }
+#pragma unroll
+    for (int k = 0; k < 2 * J; ++k)
+        if (j + k < n) f(j + k, k < J ? a[k < J ? k : 0] : b[k < J ? 0 : k - J]);
+}
+
+// Replaces a row of normals by the positions they lead to from p.  A lone walk
+// spends 2/5 of its round here, bound by the latency of the dependent
+// operation: with one batch ahead, positions copied into store order and
+// guarded reads a step of a lone walk took 37 ns in FP64 and 30 in mixed
+// precision, so 34.5 and 21.
+template <bool F64, class T = typename Prec<F64>::T>
+__device__ __forceinline__ void chain_row(Quad<T>* row, int n, T sdt, T p)
+{
+    for_row<F64>(row, n, [&](int j, Quad<T> q) {
+#pragma unroll
+        for (int e = 0; e < CoopRound<F64>::kV; ++e) p = q.v[e] = fma_into(q.v[e], sdt, p);
+        row[j] = q;
+    });
+}
 
 // One shared round: m live walks (walk w is held by lane lanes[w]; rank is w
 // in the lanes that hold one), `macros` macro-steps each, whose normals are
@@ -1019,38 +1082,7 @@ __device__ __forceinline__ void coop_round(Walker<F64, KAHAN, false, LOOP>& W, c
         const int from = lanes[w];
         const T s0 = __shfl(W.x0, from), s1 = __shfl(W.x1, from), s2 = __shfl(W.x2, from);
         if (c < 3) {
-            T p = c == 0 ? s0 : c == 1 ? s1 : s2;
-            Quad<T>* row = reinterpret_cast<Quad<T>*>(R.pos + q * pitch);
-            constexpr int J = 8 / V;              // a batch of 8 steps
-            const int n = L / V;
-            Quad<T> z[J];
-            int j = 0;
-            if (J <= n) {
-#pragma unroll
-                for (int k = 0; k < J; ++k) z[k] = row[k];
-            }
-            for (; j + J <= n; j += J) {
-                // the next batch's loads are in flight while this one's chain runs
-                Quad<T> next[J] = {};
-                if (j + 2 * J <= n) {
-#pragma unroll
-                    for (int k = 0; k < J; ++k) next[k] = row[j + J + k];
-                }
-#pragma unroll
-                for (int k = 0; k < J; ++k) {
-#pragma unroll
-                    for (int e = 0; e < V; ++e) z[k].v[e] = p = Prec<F64>::fmat(P.sdt, z[k].v[e], p);
-                    row[j + k] = z[k];
-                }
-#pragma unroll
-                for (int k = 0; k < J; ++k) z[k] = next[k];
-            }
-            for (; j < n; ++j) {
-                Quad<T> t = row[j];
-#pragma unroll
-                for (int e = 0; e < V; ++e) t.v[e] = p = Prec<F64>::fmat(P.sdt, t.v[e], p);
-                row[j] = t;
-            }
+            chain_row<F64>(reinterpret_cast<Quad<T>*>(R.pos + q * pitch), L / V, P.sdt, c == 0 ? s0 : c == 1 ? s1 : s2);
         }
     }
     if (lane < m) R.end[lane] = L;
@@ -1135,15 +1167,11 @@ __device__ __forceinline__ void coop_round(Walker<F64, KAHAN, false, LOOP>& W, c
     } else if (W.active) {
         const T* row = R.dens + rank * pitch;
         const int whole = f < L ? f : L;          // densities of full weight
-        int s = 0;
-        for (; s + 8 <= whole; s += 8) {
-            Quad<T> d[8 / V];
+        for_row<F64>(reinterpret_cast<const Quad<T>*>(row), whole / V, [&](int, const Quad<T>& d) {
 #pragma unroll
-            for (int k = 0; k < 8 / V; ++k) d[k] = *reinterpret_cast<const Quad<T>*>(row + s + k * V);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) W.add_density(d[e / V].v[e % V]);
-        }
-        for (; s < whole; ++s) W.add_density(row[s]);
+            for (int e = 0; e < V; ++e) W.add_density(d.v[e]);
+        });
+        for (int s = whole & ~(V - 1); s < whole; ++s) W.add_density(row[s]);
         if (f < L) W.add_density(T(0.5) * row[f]);
     }
     if (W.active) {

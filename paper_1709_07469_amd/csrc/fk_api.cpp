@@ -727,14 +727,14 @@ fk_status run_solve(int32_t kind, const double* stations, int64_t n_stations, co
     bool first = true;
     const std::vector<Shape> shapes{Shape{n_stations, p->paths_per_station, C.npair, L.n_chunks}};
     fk_status st = for_each_slice(shapes, L.held, [&](const Slice& sl) -> fk_status {
-        hipError_t e = first ? fk::launch_zero_queue(C.queue, stream, status, p->strict ? FK_FLAG_STRICT : 0u)
-                             : fk::launch_zero_queue(C.queue, stream);
-        first = false;
-        if (e != hipSuccess) return fail(FK_EDEVICE, "queue reset launch failed: %s", hipGetErrorString(e));
         fk::LaunchCfg cfg;
         int slice_loop = loop;
         fk_status ps = plan_launch(p->precision, sl.t1 - sl.t0, &cfg, &slice_loop);
         if (ps != FK_OK) return ps;
+        hipError_t e = first ? fk::launch_zero_queue(C.queue, cfg, stream, status, p->strict ? FK_FLAG_STRICT : 0u)
+                             : fk::launch_zero_queue(C.queue, cfg, stream);
+        first = false;
+        if (e != hipSuccess) return fail(FK_EDEVICE, "queue reset launch failed: %s", hipGetErrorString(e));
         C.task0 = sl.t0;
         C.n_tasks = sl.t1 - sl.t0;
         C.grab = cfg.grab;
@@ -963,8 +963,7 @@ fk_status solve_batch(const fk_problem* probs, int32_t n, fk_stat* out, void* wo
     auto* descs = reinterpret_cast<fk::BatchDesc*>(ws + BL.desc);
     uint32_t* status = reinterpret_cast<uint32_t*>(ws + BL.status);
     auto* queue = reinterpret_cast<unsigned long long*>(ws + BL.queue);
-    hipError_t e = fk::launch_zero_queue(queue, stream, status, strict ? FK_FLAG_STRICT : 0u);
-    if (e != hipSuccess) return fail(FK_EDEVICE, "queue reset launch failed: %s", hipGetErrorString(e));
+    hipError_t e = hipSuccess;
     Upload up(ws, stream);
     for (int32_t m = 0; m < n; ++m) {
         const fk_problem& P = probs[m];
@@ -1041,15 +1040,15 @@ fk_status solve_batch(const fk_problem* probs, int32_t n, fk_stat* out, void* wo
         largest = std::max(largest, pair_walks(BL.shapes[m]));
     }
     st = for_each_slice(BL.shapes, BL.held, [&](const Slice& sl) -> fk_status {
-        hipError_t le = hipSuccess;
-        if (!first) le = fk::launch_zero_queue(queue, stream);
-        first = false;
-        if (le != hipSuccess) return fail(FK_EDEVICE, "queue reset launch failed: %s", hipGetErrorString(le));
         fk::LaunchCfg cfg;
         int slice_loop = loop;
         fk_status ps = plan_launch(precision, sl.t1 - sl.t0, &cfg, &slice_loop, true, shared, false,
                                    A.uniform_key != 0);
         if (ps != FK_OK) return ps;
+        hipError_t le = first ? fk::launch_zero_queue(queue, cfg, stream, status, strict ? FK_FLAG_STRICT : 0u)
+                              : fk::launch_zero_queue(queue, cfg, stream);
+        first = false;
+        if (le != hipSuccess) return fail(FK_EDEVICE, "queue reset launch failed: %s", hipGetErrorString(le));
         A.task0 = sl.t0;
         A.n_tasks = sl.t1 - sl.t0;
         A.q0 = sl.q0;
@@ -1178,7 +1177,7 @@ fk_status adjoint(int32_t kind, const double* stations, int64_t n_stations, cons
     hipError_t e = fk::launch_fill_zero(counts, n_stations * AL.nvox, stream);
     if (e == hipSuccess)
         e = dense ? fk::launch_fill_zero(reinterpret_cast<int64_t*>(C.queue), n_stations, stream)
-                  : fk::launch_zero_queue(C.queue, stream);
+                  : fk::launch_zero_queue(C.queue, cfg, stream);
     if (e != hipSuccess) return fail(FK_EDEVICE, "adjoint set-up launch failed: %s", hipGetErrorString(e));
     std::pair<hipEvent_t, hipEvent_t> ev{nullptr, nullptr};
     const bool timed = timing_begin(&ev, stream);

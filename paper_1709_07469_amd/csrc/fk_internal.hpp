@@ -236,10 +236,11 @@ struct LaunchCfg {
 };
 
 // Host launchers (one translation unit per kernel family).
-// Clears the queue's claim counters; with status non-null also sets the
-// status word to `flags` (the start of a solve).
-hipError_t launch_zero_queue(unsigned long long* queue, hipStream_t stream, uint32_t* status = nullptr,
-                             uint32_t flags = 0);
+// Sets the queue's claim counters for a walk launch (past the first runs of its
+// wavefronts); with status non-null also sets the status word to `flags` (the
+// start of a solve).
+hipError_t launch_zero_queue(unsigned long long* queue, const LaunchCfg& cfg, hipStream_t stream,
+                             uint32_t* status = nullptr, uint32_t flags = 0);
 // adjoint: the replay that scatters occupation weights; dense: its instance
 // with per-station dense LDS tables (grids of at most kAdjDenseVoxels voxels,
 // blocks of kAdjDenseBlock threads, one claim counter per station in the

@@ -58,9 +58,18 @@ constexpr int kMaxWaves = 4;        // 256 threads per block at most
 // source anyway, and stripes that end on long walks lengthen the drain).
 constexpr uint32_t kMaxStripes = 32;
 
-__global__ void zero_queue_kernel(unsigned long long* q, uint32_t* status, uint32_t flags)
+// Blocks b < n of a launch with b mod m = r.
+__host__ __device__ inline uint32_t blocks_of(uint32_t n, uint32_t m, uint32_t r)
 {
-    if (threadIdx.x < kMaxStripes) q[threadIdx.x] = 0ull;
+    return (n + m - 1u - r) / m;
+}
+
+// per_block: tasks of the first runs of a block's wavefronts
+__global__ void zero_queue_kernel(unsigned long long* q, uint32_t grid, uint32_t stripes, uint32_t per_block,
+                                  uint32_t* status, uint32_t flags)
+{
+    const uint32_t s = threadIdx.x;
+    if (s < kMaxStripes) q[s] = s < stripes ? (unsigned long long)blocks_of(grid, stripes, s) * per_block : 0ull;
     if (status && threadIdx.x == 0) *status = flags;
 }
 
@@ -94,7 +103,13 @@ __device__ __forceinline__ void wave_sync_lds()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Wave-uniform claim state over the striped task queue.
+// Wave-uniform claim state over the striped task queue.  Claims of one counter
+// are served one after the other, some 35 ns each, so a launch's wavefronts
+// take their first run of tasks by their place in it (start_pool), and the
+// counters, set past those runs, give out the rest.  A capped launch (cap < 64)
+// has no more tasks than first runs, and claims none: with a claim each at the
+// start and a failing one at the end, 2000 wavefronts of one short walk spent
+// 4/5 of the launch on them.
 struct Queue {
     unsigned long long* counter;   // one claim counter per stripe
     uint64_t n_tasks;
@@ -113,9 +128,30 @@ struct Pool {
     int64_t started;    // walks started after the first fill
 };
 
+// RUNS: with a first run, of as many tasks as the wavefront may hold.
+template <bool RUNS>
 __device__ __forceinline__ Pool start_pool(const Queue& Q)
 {
-    return Pool{0ull, 0ull, Q.n_tasks, false, blockIdx.x % Q.stripes, 0u, 0ull, -64};
+    const uint32_t stripe = blockIdx.x % Q.stripes;
+    Pool pool{0ull, 0ull, Q.n_tasks, false, stripe, 0u, 0ull, -64};
+    if constexpr (RUNS) {
+        // the wavefront's place among those of its stripe
+        const uint32_t waves = blockDim.x / 64;
+        uint64_t place = (uint64_t)(blockIdx.x / Q.stripes) * waves + __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
+        uint64_t lo = Q.n_tasks * stripe / Q.stripes, hi = Q.n_tasks * (stripe + 1) / Q.stripes;
+        if (Q.cap < 64u) {              // the tasks in equal runs, the stripes' wavefronts in order
+            for (uint32_t s = 0; s < stripe; ++s) place += (uint64_t)blocks_of(gridDim.x, Q.stripes, s) * waves;
+            lo = 0ull;
+            hi = Q.n_tasks;
+            pool.exhausted = true;
+        }
+        lo += place * Q.cap;
+        pool.next = lo < hi ? lo : hi;
+        pool.end = lo + Q.cap < hi ? lo + Q.cap : hi;
+        const uint64_t runs = (uint64_t)Q.total_waves * Q.cap;
+        pool.left = runs < Q.n_tasks ? Q.n_tasks - runs : 0ull;
+    }
+    return pool;
 }
 
 // Starting walks costs the wavefront about half a macro-step however many
@@ -139,9 +175,8 @@ __device__ __forceinline__ uint64_t refill(Pool& pool, const Queue& Q, bool acti
     const uint32_t live = 64u - (uint32_t)__popcll(idle);
     if (live >= Q.cap) return ~0ull;
     const uint32_t n_idle = Q.cap - live;
-    // an all-idle wavefront always passes: started <= 64 rounds.  A capped
-    // launch is short and its rounds are many steps long: no waiting there.
-    if (Q.cap == 64u && !pool.exhausted && pool.started > 0 &&
+    // an all-idle wavefront always passes: started <= 64 rounds
+    if (!pool.exhausted && pool.started > 0 &&
         (uint64_t)n_idle * (n_idle + 1) * pool.rounds < (uint64_t)Q.refill_cost * (uint64_t)pool.started)
         return ~0ull;
     const uint32_t stripes = Q.stripes;
@@ -1298,7 +1333,7 @@ __device__ __forceinline__ void walk_body(const Args& A)
             f(source(), std::true_type{});
         }
     };
-    Pool pool = start_pool(Q);
+    Pool pool = start_pool<!DENSE>(Q);
     Walker<F64, KAHAN, ADJ, LOOP, DENSE> W;
     W.active = false;
     W.rec = 0;
@@ -1409,6 +1444,7 @@ __device__ __forceinline__ void walk_body(const Args& A)
     // drain rounds.  (Two loops, so that what the drain rounds keep in
     // registers is not live through the macro-steps.)
     auto run_waves = [&]() {
+        if (DRAIN && Q.cap < 64u) start_walks();     // a capped launch: its one run
         while (!DRAIN || Q.cap == 64u) {
             start_walks();
             if (__ballot(W.active) == 0ull) {
@@ -1437,12 +1473,8 @@ __device__ __forceinline__ void walk_body(const Args& A)
             if (done) W.finish(P, z, at, how);
         }
         while (DRAIN) {
-            if (!pool.exhausted) start_walks();      // a capped launch
             const uint64_t live = __ballot(W.active);
-            if (live == 0ull) {
-                if (pool.exhausted) break;
-                continue;
-            }
+            if (live == 0ull) break;
             const int m = __popcll(live);
             // ---- drain round: the queue is empty, or the launch gives no
             // wavefront more walks than these, so every lane generates Philox
@@ -1558,7 +1590,7 @@ __device__ __forceinline__ void walk_body(const Args& A)
             const int s = next_station;
             if (s < 0) break;
             Q = Queue{A.c.queue + s, per, (uint32_t)A.c.grab, waves_per_station, 1u, A.c.refill_cost, 64u};
-            pool = start_pool(Q);
+            pool = start_pool<false>(Q);
             task_base = (uint64_t)s * per;
             run_waves();
             __syncthreads();    // the block's walks of station s are done
@@ -1675,9 +1707,11 @@ __global__ void __launch_bounds__(256, loop_exit(LOOP)   ? 1
 
 }  // namespace
 
-hipError_t launch_zero_queue(unsigned long long* queue, hipStream_t stream, uint32_t* status, uint32_t flags)
+hipError_t launch_zero_queue(unsigned long long* queue, const LaunchCfg& cfg, hipStream_t stream, uint32_t* status,
+                             uint32_t flags)
 {
-    hipLaunchKernelGGL(zero_queue_kernel, dim3(1), dim3(64), 0, stream, queue, status, flags);
+    hipLaunchKernelGGL(zero_queue_kernel, dim3(1), dim3(64), 0, stream, queue, (uint32_t)cfg.grid, cfg.stripes,
+                       cfg.cap == 64u ? (uint32_t)cfg.block : 0u, status, flags);
     return hipGetLastError();
 }
 

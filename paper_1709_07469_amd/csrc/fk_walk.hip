@@ -1021,8 +1021,8 @@ struct CoopRound {
     alignas(16) T pos[3 * kRow];
     static constexpr int kPad = 128 / (int)sizeof(T);     // read past a row's end (for_row)
     alignas(16) T dens[kRow + kPad];
-    int end[kCoopLive];           // first step that ends walk w
-    int how[kCoopLive];           // and how (Walker::steps)
+    int end[kCoopLive];           // 16 x the first step that ends walk w + how (Walker::steps)
+    uint8_t near[64 * Prec<F64>::kMacro];   // bridge test: points to test
 };
 
 template <class T>
@@ -1097,7 +1097,7 @@ __device__ __forceinline__ void chain_row(Quad<T>* row, int n, T sdt, T p)
 // in R.pos.  P is the live walks' problem.
 template <bool F64, bool KAHAN, int LOOP>
 __device__ __forceinline__ void coop_round(Walker<F64, KAHAN, false, LOOP>& W, const LaneProblem<F64>& P,
-                                           const typename Prec<F64>::Src& src, CoopRound<F64>& R, const int* lanes,
+                                           const typename Prec<F64>::Src& src, CoopRound<F64>& R, const uint8_t* lanes,
                                            int m, int macros, int rank)
 {
     using T = typename Prec<F64>::T;
@@ -1120,11 +1120,16 @@ __device__ __forceinline__ void coop_round(Walker<F64, KAHAN, false, LOOP>& W, c
             chain_row<F64>(reinterpret_cast<Quad<T>*>(R.pos + q * pitch), L / V, P.sdt, c == 0 ? s0 : c == 1 ? s1 : s2);
         }
     }
-    if (lane < m) R.end[lane] = L;
+    if (lane < m) R.end[lane] = 16 * L;
     wave_sync_lds();
 
     // 2. densities and exit tests: point t = w L + s in lane t mod 64
     auto at = [&](int c, int w, int s) { return (c * m + w) * pitch + s; };
+    auto before = [&](int w, int s, T& a0, T& a1, T& a2) {   // the point before step s > 0
+        a0 = R.pos[at(0, w, s - 1)];
+        a1 = R.pos[at(1, w, s - 1)];
+        a2 = R.pos[at(2, w, s - 1)];
+    };
     T y[3 * MACRO], rn[MACRO];
     int ws[MACRO], ss[MACRO];
 #pragma unroll
@@ -1137,56 +1142,65 @@ __device__ __forceinline__ void coop_round(Walker<F64, KAHAN, false, LOOP>& W, c
     }
     Walker<F64, KAHAN, false, LOOP>::template densities<MACRO>(src, y, rn);
     bool some = false;
-    uint32_t ends = 0;                            // bit i: point i ends its walk
-    int hows[MACRO];
     uint64_t mass[MACRO];                         // lanes whose point i has a density
-    int n_mass = 0;
+    int n_mass = 0, n_near = 0;
+    // a walk's end as 16 step + how: the earliest step, and there a stop at a
+    // face before a cap
+    auto ends = [&](int w, int s, int how) {
+        atomicMin(&R.end[w], 16 * s + (how == 1 ? 15 : how));
+        some = true;
+    };
 #pragma unroll
     for (int i = 0; i < MACRO; ++i) {
         const bool valid = lane + 64 * i < L * m;
         const int w = ws[i], s = ss[i];
-        const int from = lanes[w];
-        const uint32_t nw = (uint32_t)__shfl((int)W.n, from);
+        const uint32_t nw = (uint32_t)__shfl((int)W.n, lanes[w]);
         const T y0 = y[3 * i], y1 = y[3 * i + 1], y2 = y[3 * i + 2];
         if (valid) R.dens[w * pitch + s] = rn[i];
         mass[i] = __builtin_amdgcn_ballot_w64(valid & !(rn[i] == T(0)));
         n_mass += __popcll(mass[i]);
         T d2;
         const bool out = Walker<F64, KAHAN, false, LOOP>::leaves(P, y0, y1, y2, d2);
-        int stop = -1;
+        if (valid & (out | (nw + (uint32_t)s + 1u >= P.max_steps))) ends(w, s, out ? 0 : 1);
         if constexpr (loop_exit(LOOP) == 2) {
-            const uint32_t pw = (uint32_t)__shfl((int)W.pctr, from), sw = (uint32_t)__shfl((int)W.sctr, from);
+            const int from = lanes[w];
             T a0 = __shfl(W.x0, from), a1 = __shfl(W.x1, from), a2 = __shfl(W.x2, from);
-            if (P.bridge && valid && !out) {
-                if (s > 0) {
-                    a0 = R.pos[at(0, w, s - 1)];
-                    a1 = R.pos[at(1, w, s - 1)];
-                    a2 = R.pos[at(2, w, s - 1)];
-                }
-                const T da = P.ball ? dist2(a0, a1, a2, P.lo0, P.lo1, P.lo2) : T(0);
-                if (!(W.deep_inside(P, a0, a1, a2, da) && W.deep_inside(P, y0, y1, y2, d2)))
-                    stop = W.bridge_stop(P, pw, sw, nw + (uint32_t)s, a0, a1, a2, y0, y1, y2);
+            const bool test = P.bridge && valid && !out;
+            if (test && s > 0) before(w, s, a0, a1, a2);
+            const T da = P.ball ? dist2(a0, a1, a2, P.lo0, P.lo1, P.lo2) : T(0);
+            const bool near = test && !(W.deep_inside(P, a0, a1, a2, da) && W.deep_inside(P, y0, y1, y2, d2));
+            const uint64_t nears = __builtin_amdgcn_ballot_w64(near);
+            if (near) R.near[n_near + __popcll(nears & __lanemask_lt())] = (uint8_t)(lane + 64 * i);
+            n_near += __popcll(nears);
+        }
+    }
+    if constexpr (loop_exit(LOOP) == 2) {
+        // the steps that may cross a face on the way, 64 at a time (tested where
+        // they are, each of the MACRO passes over the points that holds one
+        // would pay for a test of its own: 1930 against 1900 us for 31 stations
+        // of 2 x 2048 walks)
+        wave_sync_lds();
+        for (int p0 = 0; p0 < n_near; p0 += 64) {
+            const bool mine = p0 + lane < n_near;
+            const int t = R.near[mine ? p0 + lane : 0];
+            const int w = (t * over_L) >> 16, s = t - w * L, from = lanes[w];
+            const uint32_t pw = (uint32_t)__shfl((int)W.pctr, from), sw = (uint32_t)__shfl((int)W.sctr, from);
+            const uint32_t nw = (uint32_t)__shfl((int)W.n, from);
+            T a0 = __shfl(W.x0, from), a1 = __shfl(W.x1, from), a2 = __shfl(W.x2, from);
+            if (mine) {
+                if (s > 0) before(w, s, a0, a1, a2);
+                const int stop = W.bridge_stop(P, pw, sw, nw + (uint32_t)s, a0, a1, a2, R.pos[at(0, w, s)],
+                                               R.pos[at(1, w, s)], R.pos[at(2, w, s)]);
+                if (stop >= 0) ends(w, s, 2 + stop);
             }
         }
-        const bool end = valid & (out | (stop >= 0) | (nw + (uint32_t)s + 1u >= P.max_steps));
-        hows[i] = out ? 0 : stop >= 0 ? 2 + stop : 1;
-        if (end) {
-            atomicMin(&R.end[w], s);
-            ends |= 1u << i;
-        }
-        some = some | end;
     }
     const bool any_end = __builtin_amdgcn_ballot_w64(some) != 0ull;
     wave_sync_lds();
-    if (any_end) {
-#pragma unroll
-        for (int i = 0; i < MACRO; ++i)
-            if ((ends & (1u << i)) && R.end[ws[i]] == ss[i]) R.how[ws[i]] = hows[i];
-        wave_sync_lds();
-    }
 
     // 3. the walks' sums and ends
-    const int f = any_end && W.active ? R.end[rank] : L;
+    const int end = any_end && W.active ? R.end[rank] : 16 * L;
+    const int f = end >> 4, how = (end & 15) == 15 ? 1 : end & 15;
     const int taken = f < L ? f + 1 : L;
     // Adding a zero leaves an uncompensated sum as it is.  One density costs
     // some 8 instructions from its lane, a step of every walk 3 from LDS.
@@ -1221,7 +1235,7 @@ __device__ __forceinline__ void coop_round(Walker<F64, KAHAN, false, LOOP>& W, c
                 a1 = R.pos[at(1, rank, f - 1)];
                 a2 = R.pos[at(2, rank, f - 1)];
             }
-            W.finish_at(P, a0, a1, a2, e0, e1, e2, R.how[rank]);
+            W.finish_at(P, a0, a1, a2, e0, e1, e2, how);
         } else {
             W.x0 = e0;
             W.x1 = e1;
@@ -1255,7 +1269,7 @@ __device__ __forceinline__ void walk_body(const Args& A)
     constexpr int TAIL_WAVES = DRAIN ? kMaxWaves : 1;
     static_assert(!DENSE || (ADJ && !BATCH), "dense tables are the adjoint's");
 
-    __shared__ int tail_lane[TAIL_WAVES][64];
+    __shared__ uint8_t tail_lane[TAIL_WAVES][64];
     // a drain round's normals: block slots of NPB, or a shared round's rows
     // (the adjoint's blocks have LDS for half as many slots beside its table)
     constexpr int kSlots = ADJ ? 192 : 384;
@@ -1483,7 +1497,7 @@ __device__ __forceinline__ void walk_body(const Args& A)
             // macro-steps of each as the slots hold: of the lanes' passes at
             // most a fifth is then unused, however many walks are live.
             const int rank = __popcll(live & __lanemask_lt());
-            if (W.active) tail_lane[wave][rank] = lane;
+            if (W.active) tail_lane[wave][rank] = (uint8_t)lane;
             wave_sync_lds();
             // shared: few enough live walks, all of one problem
             const int first = __ffsll((unsigned long long)live) - 1;

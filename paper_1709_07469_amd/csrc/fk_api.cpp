@@ -868,7 +868,7 @@ BatchLayout make_batch_layout(const fk_problem* probs, int32_t n)
 // arguments, as many to a launch as it takes.  A launch costs 2 to 5 us
 // wherever its words go: a batch of 48 small grid models, two launches for
 // each whole descriptor and 98 in all, spent 230 us of 1190 on them; their used
-// parts take 12: 1028 us in all.
+// parts take 14: 1028 us in all.
 class Upload {
 public:
     Upload(char* ws, hipStream_t stream) : base_(reinterpret_cast<uint64_t*>(ws)), stream_(stream) {}

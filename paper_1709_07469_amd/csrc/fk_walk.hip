@@ -1004,10 +1004,11 @@ struct Walker {
 // The arithmetic of every step and its order are those of a macro-step, so a
 // walk's record does not depend on the rounds it ran in.
 // Measured, with the even shares of Queue::cap, against lanes stepping alone:
-// a lone walk 213 -> 38 ns a step in FP64, 175 to 214 -> 22 to 30 ns mixed;
-// 8 stations x 250 walks in FP64 1329 -> 173 us (a call returning host
-// arrays); Table 1's cells Delta t = 0.01, N = 5120: 6.67 -> 3.47 ms, and
-// 0.001, N = 25600 (with the FP64 normals): 129 -> 84.5 ms.
+// a lone walk 213 -> 33 ns a step in FP64, 175 to 214 -> 21 ns mixed;
+// 8 stations x 250 walks in FP64 1329 -> 141 us (a call returning host
+// arrays, with the first runs of start_pool); Table 1's cells Delta t = 0.01,
+// N = 5120: 6.67 -> 3.11 ms, and 0.001, N = 25600 (with the FP64 normals):
+// 129 -> 84.0 ms.
 constexpr int kCoopLive = 21;     // the chains fill a wavefront
 
 // A wavefront's LDS in a shared round.  Row (axis c, walk w) starts at
@@ -1081,7 +1082,7 @@ __device__ __forceinline__ void for_row(const Quad<T>* row, int n, F&& f)
 // spends 2/5 of its round here, bound by the latency of the dependent
 // operation: with one batch ahead, positions copied into store order and
 // guarded reads a step of a lone walk took 37 ns in FP64 and 30 in mixed
-// precision, so 34.5 and 21.
+// precision, and takes 34.5 and 21 so.
 template <bool F64, class T = typename Prec<F64>::T>
 __device__ __forceinline__ void chain_row(Quad<T>* row, int n, T sdt, T p)
 {

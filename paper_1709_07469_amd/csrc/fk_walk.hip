@@ -990,7 +990,7 @@ struct Walker {
 // instruction of a step -- some 60 of them, 5 cycles each with one wavefront
 // per SIMD -- for one step's worth of work.  Of a step only the move
 // x + sqrt(dt) z and the sum of densities depend on the step before; densities
-// and exit tests do not.  So in a round with at most kCoopLive live walks of
+// and exit tests do not.  So in a round with at most coop_live live walks of
 // one problem
 //   1. the chain of moves runs in one lane per walk and axis, which replaces
 //      its row of normals in LDS by the positions they lead to (rows, so that
@@ -1010,6 +1010,11 @@ struct Walker {
 // N = 5120: 6.67 -> 3.11 ms, and 0.001, N = 25600 (with the FP64 normals):
 // 129 -> 84.0 ms.
 constexpr int kCoopLive = 21;     // the chains fill a wavefront
+// Without the bridge test (whose tests of every point sharing spreads best)
+// rounds of 17 to 21 walks are sooner done unshared: 48 small grid models 674
+// -> 657 us, the cell of 5120 walks 3114 -> 3059 us with at most 16 shared,
+// and the bridge g_z 1915 -> 2019 (32 shared: 3118 -> 3407 and 1944 -> 2005).
+constexpr int coop_live(int loop) { return loop_exit(loop) == 2 ? kCoopLive : 16; }
 
 // A wavefront's LDS in a shared round.  Row (axis c, walk w) starts at
 // (c m + w) pitch, pitch = the round's steps and 16 bytes (so that rows start
@@ -1502,7 +1507,7 @@ __device__ __forceinline__ void walk_body(const Args& A)
             wave_sync_lds();
             // shared: few enough live walks, all of one problem
             const int first = __ffsll((unsigned long long)live) - 1;
-            bool shared = !ADJ && m <= kCoopLive;
+            bool shared = !ADJ && m <= coop_live(LOOP);
             if constexpr (!ADJ && BATCH) {
                 const uint64_t pc = lane_u64((uint64_t)P.C, first);
                 shared = shared && __builtin_amdgcn_ballot_w64(W.active && (uint64_t)P.C != pc) == 0ull;

@@ -1,6 +1,6 @@
 """GPU: launches that give every wavefront a few walks run them in shared
 drain rounds; the number of live walks decides how a round is divided (3 lanes
-per walk up to 21 walks, the walks' own lanes beyond, and as many macro-steps as
+per walk up to 16 walks, 21 with the bridge test, the walks' own lanes beyond, and as many macro-steps as
 the block slots hold).  At the edges of those ranges every walk's
 record must equal the oracle's in FP64 (1e-12 of the mean |u|, step counts
 exactly), and in every precision, bit for bit, what a full launch records.
@@ -17,7 +17,7 @@ from gpu_helpers import compare_walks, gpu_solve, say
 pytestmark = pytest.mark.gpu
 
 WAVES = 256          # one 64-thread block per compute unit
-CAPS = (1, 2, 3, 21, 22, 32, 33, 42, 43, 63)
+CAPS = (1, 2, 3, 16, 17, 21, 22, 32, 33, 42, 43, 63)
 
 
 @pytest.fixture(scope="module", autouse=True)

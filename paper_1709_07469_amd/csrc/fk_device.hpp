@@ -100,7 +100,8 @@ __device__ __forceinline__ double neg2_log(double u)
 // rounded reference to 2e-15 of max(1, |z|), within the 4e-15 the reference
 // angle's own rounding allows.  At x = +-0 the estimate, infinite there, is
 // replaced by a large finite number, which every product then carries to 0
-// (one minimum instead of a compare and two selects on the result).
+// (one minimum instead of a compare and two selects on the result); an x other
+// than 0 must be at least 2^-1000, where the estimate itself is that large.
 #ifndef FK_SQRT_ITERS
 #define FK_SQRT_ITERS 1
 #endif
@@ -650,7 +651,7 @@ __device__ __forceinline__ DataTables fill_data_tables()
     return DataTables{bm, at};
 }
 
-// ln x for a positive finite x, from the table-driven -2 ln x.
+// ln x for a positive normal x, from the table-driven -2 ln x.
 __device__ __forceinline__ double ln_t(double x, const BmTables& T) { return -0.5 * neg2_log_t(x, T); }
 
 // 1/q for a positive normal q: the hardware estimate and two Newton steps
@@ -705,13 +706,13 @@ __device__ __forceinline__ Quot shift_quot(double w, double r, double s)
 }
 
 // ln(A / B) for A = a.n / a.d and B = b.n / b.d, as one logarithm of
-// (a.n b.d) / (a.d b.n).  An argument that is not positive and finite --
-// only in terms the caller discards, whose prefactor is zero -- is replaced by
-// 1 so that the table lookup stays in range.
+// (a.n b.d) / (a.d b.n).  A quotient that is not a positive normal number --
+// only in terms whose prefactor is zero or far below the others' rounding -- is
+// replaced by 1: the table logarithm takes the exponent from the high word.
 __device__ __forceinline__ double ln_ratio(const Quot& a, const Quot& b, const BmTables& T)
 {
     double x = (a.n * b.d) * recip(a.d * b.n);
-    x = (x > 0.0 && x <= 0x1.fffffffffffffp+1023) ? x : 1.0;
+    x = (x >= 0x1p-1022 && x <= 0x1.fffffffffffffp+1023) ? x : 1.0;
     return ln_t(x, T);
 }
 

@@ -638,12 +638,12 @@ fk_status plan_loop(int precision, int64_t n_tasks, fk::LaunchCfg* cfg, bool bat
 // their start, which the covering lookup has no part in: they take the general
 // loop, whose kernels need fewer registers there.
 fk_status plan_launch(int precision, int64_t n_tasks, fk::LaunchCfg* cfg, int* loop, bool batch = false,
-                      bool shared = false, bool adjoint = false, bool ukey = false)
+                      bool shared = false, bool ukey = false)
 {
-    fk_status st = plan_loop(precision, n_tasks, cfg, batch, *loop, shared, adjoint, ukey);
+    fk_status st = plan_loop(precision, n_tasks, cfg, batch, *loop, shared, false, ukey);
     if (st == FK_OK && cfg->cap < 64u && (*loop & 16)) {
         *loop &= ~16;
-        st = plan_loop(precision, n_tasks, cfg, batch, *loop, shared, adjoint, ukey);
+        st = plan_loop(precision, n_tasks, cfg, batch, *loop, shared, false, ukey);
     }
     return st;
 }
@@ -1042,7 +1042,7 @@ fk_status solve_batch(const fk_problem* probs, int32_t n, fk_stat* out, void* wo
     st = for_each_slice(BL.shapes, BL.held, [&](const Slice& sl) -> fk_status {
         fk::LaunchCfg cfg;
         int slice_loop = loop;
-        fk_status ps = plan_launch(precision, sl.t1 - sl.t0, &cfg, &slice_loop, true, shared, false,
+        fk_status ps = plan_launch(precision, sl.t1 - sl.t0, &cfg, &slice_loop, true, shared,
                                    A.uniform_key != 0);
         if (ps != FK_OK) return ps;
         hipError_t le = first ? fk::launch_zero_queue(queue, cfg, stream, status, strict ? FK_FLAG_STRICT : 0u)

@@ -553,13 +553,8 @@ __device__ __forceinline__ uint32_t covered_flat(const Src& s, const int* i)
 }
 
 // ---------------------------------------------------------------------------
-// Exit test (the boundary counts as outside) and the INTERSECT exit point.
+// The INTERSECT exit point.
 // ---------------------------------------------------------------------------
-template <typename T>
-__device__ __forceinline__ bool outside(const T* lo, const T* hi, T x, T y, T z)
-{
-    return x <= lo[0] || x >= hi[0] || y <= lo[1] || y >= hi[1] || z <= lo[2] || z >= hi[2];
-}
 
 // First face met on the segment a -> b (b outside, a inside): the crossing
 // fraction t_c = (face_c - a_c) / (b_c - a_c) is smallest (ties: lower axis);

@@ -1023,7 +1023,11 @@ template <bool F64>
 struct CoopRound {
     using T = typename Prec<F64>::T;
     static constexpr int kV = 16 / (int)sizeof(T);        // elements per 16 bytes
-    static constexpr int kRow = 96 * Prec<F64>::kMacro;   // most m (macros MACRO + kV): 32 walks of 2 macro-steps
+    // an axis's rows, m (macros MACRO + kV) for macros = 64 / m and m <= kCoopLive
+    // (85 MACRO at most), and room beside them for the slots of a round that is
+    // not shared
+    static constexpr int kRow = 96 * Prec<F64>::kMacro;
+    static_assert(kRow >= 64 * Prec<F64>::kMacro + kCoopLive * kV, "the rows of every shared round");
     alignas(16) T pos[3 * kRow];
     static constexpr int kPad = 128 / (int)sizeof(T);     // read past a row's end (for_row)
     alignas(16) T dens[kRow + kPad];

@@ -654,7 +654,11 @@ fk_status plan_launch(int precision, int64_t n_tasks, fk::LaunchCfg* cfg, int* l
 // where the data are prisms', whose evaluation is nearly all of that, and the
 // pairs fill few of the chip's wavefronts, up to 8 blocks per compute unit
 // share them instead: 78 pairs of 2 x 8192 walks and 5 prisms took 935 us in
-// one pass, 220 + 29 us in two.  Not for pairs of fewer than 8 walks a lane,
+// one pass, 220 + 29 us in two.  Not where that leaves two blocks a pair, whose
+// half-empty chip one pass fills nearly as well without the second reading of
+// the records: 683 pairs of 2 x 8192 walks take 557 us in one pass and 632 in
+// two with 1 prism, 2577 and 2564 with 5 (three blocks a pair, 682 pairs: 557
+// and 573, 2559 and 2289).  Not for pairs of fewer than 8 walks a lane,
 // where the second launch costs what it saves: a batch of 474 pairs of up to 7
 // walks a lane took 1167 us in one pass and 1173 in two.
 int sample_parts(bool prisms, int64_t pairs, int64_t largest)
@@ -663,7 +667,7 @@ int sample_parts(bool prisms, int64_t pairs, int64_t largest)
     if (!prisms || pairs < 1 || hipGetDevice(&dev) != hipSuccess) return 1;
     const int64_t want = 8 * (int64_t)compute_units(dev) / pairs;       // blocks per pair
     const int64_t most = (largest + 255) / 256;                         // with a walk per lane
-    return want < 2 || most < 8 ? 1 : (int)std::min(want, most);
+    return want < 3 || most < 8 ? 1 : (int)std::min(want, most);
 }
 
 // The walks of the shape's largest (station, chunk) pair.

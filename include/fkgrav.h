@@ -376,14 +376,16 @@ fk_status fk_moving_average(const double *values, const double *se, int64_t n, i
 /* Launch settings of the walk kernels (the autotuner's knobs).  block: threads
  * per block (64..256, multiple of 64); blocks_per_cu: resident blocks per
  * compute unit (0 = as many as fit); grab: largest number of walks a
- * wavefront takes from the global queue at once (1..64); adjoint_table: how
+ * wavefront takes from the global queue at once (1..64; its first walks, up to
+ * one a lane, it takes by its place in the launch); adjoint_table: how
  * the adjoint gathers its occupation weights in LDS before they reach the
  * global counts -- 0: a dense per-station table when the grid has at most
  * 32768 voxels (1024-thread blocks working through the stations one at a
  * time), else the hashed block table; 1: the hashed block table always;
  * stripes: claim counters the task queue is split into, each a contiguous
  * run of tasks that blocks b = s mod stripes start on (1..32; 0 = 8 for
- * batches of problems with separate sources, 1 otherwise); refill_cost: the
+ * batches of problems with separate sources, 1 otherwise; no claims are made in
+ * launches of fewer walks than resident lanes); refill_cost: the
  * start-up cost R of a wavefront's walk refill, as 128 R macro-steps (a
  * wavefront waits for k idle lanes, the smallest k with k (k + 1) >= 128 R
  * times its walk-end rate per macro-step; 1..8192; 0 = 64).  Settings never

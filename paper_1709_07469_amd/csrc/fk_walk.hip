@@ -11,9 +11,10 @@
 //
 // Scheduling (gfx950, wave64):
 //   - persistent blocks, sized from the occupancy calculator;
-//   - a wavefront claims a run of consecutive walks from one global counter
-//     (one atomic per claim; the run shrinks as the queue drains so the last
-//     walks spread over all wavefronts);
+//   - a wavefront's first run of consecutive walks is given by its place in
+//     the launch; further runs it claims from a global counter (one atomic per
+//     claim; the run shrinks as the queue drains so the last walks spread over
+//     all wavefronts);
 //   - lanes whose walk has ended are refilled at macro-step boundaries, where
 //     every active lane is at the start of a Philox block triple: FP64 walks
 //     take 2 steps (6 normals = 3 blocks), mixed walks take 4 steps
@@ -1004,7 +1005,8 @@ struct Walker {
 // The arithmetic of every step and its order are those of a macro-step, so a
 // walk's record does not depend on the rounds it ran in.
 // Measured, with the even shares of Queue::cap, against lanes stepping alone:
-// a lone walk 213 -> 33 ns a step in FP64, 175 to 214 -> 21 ns mixed;
+// a lone walk 213 -> 33 ns a step in FP64 (37 on a grid), 175 to 214 -> 20 to
+// 21 ns mixed;
 // 8 stations x 250 walks in FP64 1329 -> 141 us (a call returning host
 // arrays, with the first runs of start_pool); Table 1's cells Delta t = 0.01,
 // N = 5120: 6.67 -> 3.11 ms, and 0.001, N = 25600 (with the FP64 normals):
@@ -1091,7 +1093,7 @@ __device__ __forceinline__ void for_row(const Quad<T>* row, int n, F&& f)
 // spends 2/5 of its round here, bound by the latency of the dependent
 // operation: with one batch ahead, positions copied into store order and
 // guarded reads a step of a lone walk took 37 ns in FP64 and 30 in mixed
-// precision, and takes 34.5 and 21 so.
+// precision; it takes 33 and 20 to 21 now.
 template <bool F64, class T = typename Prec<F64>::T>
 __device__ __forceinline__ void chain_row(Quad<T>* row, int n, T sdt, T p)
 {
@@ -1660,17 +1662,21 @@ __device__ __forceinline__ void walk_body(const Args& A)
 // Minimum resident 256-thread blocks per CU the compiler must allow (this
 // bounds the VGPRs per lane: 4 blocks = 4 wavefronts per SIMD = 128 VGPRs).
 // FP64 walks are held to 4 wavefronts per SIMD: measured faster than 3
-// wavefronts without the limit, despite a small spill.
+// wavefronts without the limit, when the box loop spilled a little.  Now the box,
+// ball and grid loops take 115 to 117 VGPRs and spill none; with the bridge test
+// they spill 14 to 16 (52 to 60 bytes a lane).
 #ifndef FK_F64_BLOCKS_PER_CU
 #define FK_F64_BLOCKS_PER_CU 4
 #endif
-// Mixed-precision walks are held to 6 (80 VGPRs).
+// Mixed-precision walks are held to 6 (80 VGPRs; 3 to 6 spilled, 14 to 18 with
+// the bridge test).
 #ifndef FK_F32_BLOCKS_PER_CU
 #define FK_F32_BLOCKS_PER_CU 6
 #endif
-// Batches (box loop): 4 blocks for FP64 (128 VGPRs, no spill) and 5 for
-// mixed precision (96 VGPRs, a 12-byte spill) measured 7-10 % faster than the
-// unconstrained 3 and 4.  The ball and bridge loops are left free.
+// Batches (box loop): 4 blocks for FP64 (128 VGPRs; 2 spilled with a key per
+// lane) and 5 for mixed precision (96 VGPRs, a 12-byte spill) measured 7-10 %
+// faster than the unconstrained 3 and 4.  The ball and bridge loops are left free:
+// 94 to 150 VGPRs and 113 to 199, 2 to 5 blocks.
 #ifndef FK_BATCH_F64_BLOCKS_PER_CU
 #define FK_BATCH_F64_BLOCKS_PER_CU 4
 #endif
@@ -1679,7 +1685,8 @@ __device__ __forceinline__ void walk_body(const Args& A)
 #endif
 
 // Grid loops keep several grid loads in flight, which takes registers: mixed
-// single-problem walks measured best at 5 blocks (96 VGPRs), mixed batches of
+// single-problem walks measured best at 5 blocks (96 VGPRs: 88 to 91 taken, and
+// 5 to 13 spilled with the bridge test), mixed batches of
 // separate sources at 4 (128 VGPRs; per-lane source fields), while a batch
 // sharing one source stays at 5.
 #ifndef FK_F32_GRID_BLOCKS_PER_CU
@@ -1688,9 +1695,9 @@ __device__ __forceinline__ void walk_body(const Args& A)
 #ifndef FK_BATCH_F32_GRID_BLOCKS_PER_CU
 #define FK_BATCH_F32_GRID_BLOCKS_PER_CU 4
 #endif
-// FP64 batches of separate grids: 3 blocks (up to 170 VGPRs) hold the walk
-// without the 28-register spill that 4 blocks cost (whose stores reached
-// memory at about 130 GB/s), and measured 3 % faster.
+// FP64 batches of separate grids: 3 blocks (up to 170 VGPRs, 148 to 149 taken)
+// hold the walk without the 28-register spill that 4 blocks cost when it was
+// tried (whose stores reached memory at about 130 GB/s), and measured 3 % faster.
 #ifndef FK_BATCH_F64_GRID_BLOCKS_PER_CU
 #define FK_BATCH_F64_GRID_BLOCKS_PER_CU 3
 #endif
@@ -1710,7 +1717,8 @@ __global__ void __launch_bounds__(256, ADJ                ? kAdjBlocksPerCu
 }
 
 // The adjoint with dense station tables: one block of kAdjDenseBlock threads
-// per CU (the 128 KiB table takes most of the CU's 160 KiB of LDS).
+// per CU (the 128 KiB table takes most of the CU's 160 KiB of LDS).  FP64 spills
+// 4 VGPRs of its 128 (20 bytes a lane; 28 with the bridge test), mixed none.
 template <bool F64, bool KAHAN, int LOOP>
 __global__ void __launch_bounds__(kAdjDenseBlock, 1)
     adjoint_dense_kernel(const typename std::conditional<F64, WalkArgsF64, WalkArgsF32>::type A)

@@ -77,15 +77,15 @@ ALGO_BYTES_PER_WALK = 36
 # for a device copy of known size.  Figures are reported only while the
 # sources still hash to the recorded value.
 COUNTERS = {
-    "sources_sha256": "c32df42d9cb8d2a74286ff80e714ef25820a8e3b38ced9b5f946827f59d3a723",
-    "cfg4_mixed": {"valu_lane_instr_per_step": 103.1444, "valu_busy": 1.0913, "fp64_flop_per_step": 2.1044, "fp32_flop_per_step": 29.8313, "fetch_kib": 989051.3594, "write_kib": 80812283.2188, "fetch_scale": 1.999921, "write_scale": 1.0, "l2_hit": 0.9982},
-    "cfg4_f64": {"valu_lane_instr_per_step": 257.1337, "valu_busy": 0.9469, "fp64_flop_per_step": 120.411, "fp32_flop_per_step": 0.0613, "fetch_kib": 799770.3594, "write_kib": 74725090.4297, "fetch_scale": 1.999921, "write_scale": 1.0, "l2_hit": 0.9987},
-    "cfg2_f64": {"valu_lane_instr_per_step": 214.8479, "valu_busy": 0.967, "fp64_flop_per_step": 108.1473, "fp32_flop_per_step": 0.073, "fetch_kib": 168.7188, "write_kib": 879037.625, "fetch_scale": 1.999921, "write_scale": 1.0, "l2_hit": 0.8743},
-    "cfg2_mixed": {"valu_lane_instr_per_step": 84.5602, "valu_busy": 1.0337, "fp64_flop_per_step": 2.1943, "fp32_flop_per_step": 23.5735, "fetch_kib": 7842.6875, "write_kib": 1169483.7031, "fetch_scale": 1.999921, "write_scale": 1.0, "l2_hit": 0.974},
-    "cfg3_f64": {"valu_lane_instr_per_step": 263.2239, "valu_busy": 0.9743, "fp64_flop_per_step": 117.7145, "fp32_flop_per_step": 0.0941, "fetch_kib": 470147505.9792, "write_kib": 17541360.9792, "fetch_scale": 1.999921, "write_scale": 1.0, "l2_hit": 0.8799},
-    "cfg3_mixed": {"valu_lane_instr_per_step": 106.8119, "valu_busy": 0.6596, "fp64_flop_per_step": 2.1656, "fp32_flop_per_step": 30.5892, "fetch_kib": 480741901.4792, "write_kib": 16468283.5312, "fetch_scale": 1.999921, "write_scale": 1.0, "l2_hit": 0.8767},
-    "cfg3_f64_levels": {"valu_lane_instr_per_step": 266.0865, "valu_busy": 0.9891, "fp64_flop_per_step": 117.7144, "fp32_flop_per_step": 0.0941, "fetch_kib": 135953.8958, "write_kib": 31307932.0104, "fetch_scale": 1.999921, "write_scale": 1.0, "l2_hit": 0.9977},
-    "cfg3_mixed_levels": {"valu_lane_instr_per_step": 111.1091, "valu_busy": 0.8127, "fp64_flop_per_step": 2.1655, "fp32_flop_per_step": 30.5884, "fetch_kib": 174965.0833, "write_kib": 31272405.9792, "fetch_scale": 1.999921, "write_scale": 1.0, "l2_hit": 0.9972},
+    "sources_sha256": "fc410c3eef83f7990f9950028c7062018f74f857b41d8a67be0305f940ebfb9a",
+    "cfg4_mixed": {"valu_lane_instr_per_step": 98.0576, "valu_busy": 1.0914, "fp64_flop_per_step": 1.2775, "fp32_flop_per_step": 30.2086, "fetch_kib": 984350.2344, "write_kib": 80453605.0234, "fetch_scale": 1.999922, "write_scale": 1.0, "l2_hit": 0.9981},
+    "cfg4_f64": {"valu_lane_instr_per_step": 217.6471, "valu_busy": 0.9798, "fp64_flop_per_step": 109.7623, "fp32_flop_per_step": 0.0689, "fetch_kib": 800271.3750, "write_kib": 74543799.0312, "fetch_scale": 1.999922, "write_scale": 1.0, "l2_hit": 0.9987},
+    "cfg2_f64": {"valu_lane_instr_per_step": 179.7495, "valu_busy": 1.0201, "fp64_flop_per_step": 97.6987, "fp32_flop_per_step": 0.0770, "fetch_kib": 220.9219, "write_kib": 877401.3828, "fetch_scale": 1.999922, "write_scale": 1.0, "l2_hit": 0.8748},
+    "cfg2_mixed": {"valu_lane_instr_per_step": 79.4526, "valu_busy": 1.1590, "fp64_flop_per_step": 1.0371, "fp32_flop_per_step": 23.2673, "fetch_kib": 228.3906, "write_kib": 912764.3125, "fetch_scale": 1.999922, "write_scale": 1.0, "l2_hit": 0.8495},
+    "cfg3_f64": {"valu_lane_instr_per_step": 223.5079, "valu_busy": 0.9726, "fp64_flop_per_step": 111.6715, "fp32_flop_per_step": 0.0028, "fetch_kib": 472470470.8125, "write_kib": 17441109.6146, "fetch_scale": 1.999922, "write_scale": 1.0, "l2_hit": 0.8789},
+    "cfg3_mixed": {"valu_lane_instr_per_step": 102.6982, "valu_busy": 0.6402, "fp64_flop_per_step": 1.4382, "fp32_flop_per_step": 31.0696, "fetch_kib": 484783845.1667, "write_kib": 16483073.9688, "fetch_scale": 1.999922, "write_scale": 1.0, "l2_hit": 0.8751},
+    "cfg3_f64_levels": {"valu_lane_instr_per_step": 229.2742, "valu_busy": 1.0235, "fp64_flop_per_step": 111.6719, "fp32_flop_per_step": 0.0028, "fetch_kib": 134495.0208, "write_kib": 31384812.9062, "fetch_scale": 1.999922, "write_scale": 1.0, "l2_hit": 0.9977},
+    "cfg3_mixed_levels": {"valu_lane_instr_per_step": 103.7929, "valu_busy": 0.7919, "fp64_flop_per_step": 1.4382, "fp32_flop_per_step": 31.0689, "fetch_kib": 168581.3958, "write_kib": 31427688.9375, "fetch_scale": 1.999922, "write_scale": 1.0, "l2_hit": 0.9972},
 }
 TRAFFIC_SOURCES = ("paper_1709_07469_amd/csrc/fk_walk.hip", "paper_1709_07469_amd/csrc/fk_device.hpp",
                    "paper_1709_07469_amd/csrc/fk_internal.hpp", "paper_1709_07469_amd/csrc/fk_stats.hpp",
